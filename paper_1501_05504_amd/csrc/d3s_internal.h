@@ -114,6 +114,25 @@ void gemm_f64(Ctx* c, const GemmArgs& g);
 void gemm_f32(Ctx* c, const GemmArgs& g);
 void gemm_bf16(Ctx* c, const GemmArgs& g);   // bf16 operands, fp32 C
 void gemm(Ctx* c, d3s_prec p, const GemmArgs& g);
+// C = alpha * sum_z part[z] + beta * C over `splits` partial products of M x N
+void splitk_reduce(Ctx* c, bool f64, const void* part, int splits, int M, int N, void* C, long ldc, double alpha,
+                   double beta);
+// Tile configuration (2, 3; -1: the wave tiles of direct.hip) and split of K
+// for a large product, with its modelled time
+struct GemmChoice {
+  int cfg, splits;
+  double seconds;
+};
+GemmChoice gemm_estimate(d3s_prec p, int M, int N, int K);
+// The product on wave tiles (direct.hip), FP64 and FP32; false: a leading
+// dimension or batch beyond its range, nothing was launched.
+bool gemm_direct(Ctx* c, d3s_prec p, const GemmArgs& g);
+// First GEMM and W-map of a left-to-right (T1 = env psi over the left bond;
+// out[(a,s)*ld_out + v*mr + y]) or right-to-left contraction (Y = psi env^T
+// over the right bond; out[w, x, s, b]) in one launch, scaled by alpha; false
+// (nothing launched) where the separate kernels are faster or d, w do not fit.
+bool front_wmap(Ctx* c, d3s_prec p, d3s_dir dir, int ml, int d, int mr, int wl, int wr, const void* env,
+                const void* W, const void* psi, void* out, long ld_out, double alpha);
 
 // ---------------------------------------------------------------- grouped GEMM
 // One output block per task, sum over the task's K-segments (see grouped.hip).

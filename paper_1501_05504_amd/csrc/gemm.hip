@@ -84,11 +84,12 @@ void gemm_kernel(KParams p) {
 
   Stager<S, BM, NT, AKC> ga;
   Stager<S, BN, NT, BKC> gb;
+  ga.init_full(p.lda, m0, p.M);
+  gb.init_full(p.ldb, n0, p.N);
   const int nk = (kend - kbeg + BK - 1) / BK;
-  // k-tiles [0, nfull) of an interior tile load without bounds tests
+  // k-tiles [0, nfull) load without tests per element
   int nfull = 0;
-  if (nk > 0 && Stager<S, BM, NT, AKC>::full_ok(A, p.lda, m0, p.M, kbeg, kend) &&
-      Stager<S, BN, NT, BKC>::full_ok(B, p.ldb, n0, p.N, kbeg, kend))
+  if (nk > 0 && Stager<S, BM, NT, AKC>::full_ok(p.lda, m0, p.M) && Stager<S, BN, NT, BKC>::full_ok(p.ldb, n0, p.N))
     nfull = (kend - kbeg) / BK;
   auto fetch = [&](int t) {
     const int k0 = kbeg + t * BK;
@@ -263,13 +264,7 @@ void launch_cfg(Ctx* c, const GemmArgs& g, int splits) {
   else
     hipLaunchKernelGGL((gemm_kernel<S, BM, BN, WM, WN, false, false>), grid, block, 0, c->stream, p);
   D3S_HIP(hipGetLastError());
-  if (splits > 1) {
-    long total = (long)g.M * g.N;
-    long nb = std::min<long>((total + 255) / 256, 4096);
-    hipLaunchKernelGGL((splitk_reduce_kernel<AT>), dim3((unsigned)nb), dim3(256), 0, c->stream, part, splits,
-                       (long)g.M * g.N, g.M, g.N, (AT*)g.C, g.ldc, g.alpha, g.beta);
-    D3S_HIP(hipGetLastError());
-  }
+  if (splits > 1) splitk_reduce(c, sizeof(AT) == 8, part, splits, g.M, g.N, g.C, g.ldc, g.alpha, g.beta);
 }
 
 // Tile configurations (block tile / wave tile / waves):
@@ -317,8 +312,45 @@ void gemm_dispatch(Ctx* c, const GemmArgs& g) {
 
 }  // namespace
 
-void gemm_f64(Ctx* c, const GemmArgs& g) { gemm_dispatch<double>(c, g); }
-void gemm_f32(Ctx* c, const GemmArgs& g) { gemm_dispatch<float>(c, g); }
+void splitk_reduce(Ctx* c, bool f64, const void* part, int splits, int M, int N, void* C, long ldc, double alpha,
+                   double beta) {
+  const long total = (long)M * N;
+  const dim3 grid((unsigned)std::min<long>((total + 255) / 256, 4096)), block(256);
+  if (f64)
+    hipLaunchKernelGGL((splitk_reduce_kernel<double>), grid, block, 0, c->stream, (const double*)part, splits, total,
+                       M, N, (double*)C, ldc, alpha, beta);
+  else
+    hipLaunchKernelGGL((splitk_reduce_kernel<float>), grid, block, 0, c->stream, (const float*)part, splits, total, M,
+                       N, (float*)C, ldc, alpha, beta);
+  D3S_HIP(hipGetLastError());
+}
+
+namespace {
+
+// FP64 and FP32 without a chosen tile configuration: wave tiles while the
+// product has fewer than 4096 tiles of 32x32 (four a SIMD), the least
+// modelled time above
+template <typename S>
+void gemm_auto(Ctx* c, d3s_prec p, const GemmArgs& g) {
+  if (c->tile_config < 0) {
+    const double t32 = std::ceil(g.M / 32.0) * std::ceil(g.N / 32.0) * g.batch;
+    if (t32 < 4096 || g.batch > 1) {
+      if (gemm_direct(c, p, g)) return;
+    } else {
+      const GemmChoice ch = gemm_estimate(p, g.M, g.N, g.K);
+      if (ch.cfg < 0 && gemm_direct(c, p, g)) return;
+      const int splits = c->splitk_off ? 1 : ch.splits;
+      if (ch.cfg == 2) return launch_cfg<S, 256, 128, 64, 64>(c, g, splits);
+      if (ch.cfg == 3) return launch_cfg<S, 128, 128, 64, 32>(c, g, splits);
+    }
+  }
+  gemm_dispatch<S>(c, g);
+}
+
+}  // namespace
+
+void gemm_f64(Ctx* c, const GemmArgs& g) { gemm_auto<double>(c, D3S_F64, g); }
+void gemm_f32(Ctx* c, const GemmArgs& g) { gemm_auto<float>(c, D3S_F32, g); }
 void gemm_bf16(Ctx* c, const GemmArgs& g) { gemm_dispatch<bf16_t>(c, g); }
 
 void gemm(Ctx* c, d3s_prec p, const GemmArgs& g) {

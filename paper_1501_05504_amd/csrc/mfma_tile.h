@@ -140,18 +140,46 @@ struct Stager {
     }
   }
 
-  // Interior tiles: every chunk in bounds and 16-byte aligned (the caller
-  // checks this once per tile with wave-uniform values), so the loads carry
-  // no per-element tests and no divergent branches.
-  __device__ __forceinline__ void load_full(const S* __restrict__ X, long ld, int o0, int k0) {
+  // K tiles that need no test per element (full_ok): the loads carry no
+  // divergent branches, only 32-bit byte offsets (computed once) from a
+  // uniform base that moves along K.  Rows past the operand's edge are clamped
+  // to its last row (their products are not stored); a chunk need not be
+  // 16-byte aligned.
+  unsigned voff[LPT];
+  __device__ __forceinline__ void init_full(long ld, int o0, int Odim) {
 #pragma unroll
     for (int p = 0; p < LPT; ++p) {
       const int c = threadIdx.x + p * NT;
-      int o, k;
-      if constexpr (KC) { o = c / (BK / VE); k = (c % (BK / VE)) * VE; }
-      else { k = c / (O / VE); o = (c % (O / VE)) * VE; }
-      const S* src = KC ? X + (long)(o0 + o) * ld + (k0 + k) : X + (long)(k0 + k) * ld + (o0 + o);
-      r[p] = *reinterpret_cast<const uint4*>(src);
+      if constexpr (KC) {
+        const int o = c / (BK / VE), k = (c % (BK / VE)) * VE;
+        voff[p] = (unsigned)((min(o, Odim - 1 - o0) * ld + k) * (long)sizeof(S));
+      } else {
+        const int k = c / (O / VE), o = (c % (O / VE)) * VE;
+        voff[p] = (unsigned)((k * ld + o) * (long)sizeof(S));
+      }
+    }
+  }
+  // whether the offsets stay inside the buffer resource
+  __host__ __device__ static bool full_fits(long ld) { return ld <= (1L << 30) / (256 * (long)sizeof(S)); }
+  __device__ __forceinline__ void load_full(const S* __restrict__ X, long ld, int o0, int k0) {
+    const S* base = KC ? X + (long)o0 * ld + k0 : X + (long)k0 * ld + o0;
+    if constexpr (sizeof(S) >= 4) {
+      // a buffer load needs 4-byte alignment, and its base no vector registers
+      typedef unsigned u4v __attribute__((ext_vector_type(4)));
+      const __amdgpu_buffer_rsrc_t rs =
+          __builtin_amdgcn_make_buffer_rsrc(const_cast<S*>(base), (short)0, 0x7fffffff, 0x00020000);
+#pragma unroll
+      for (int p = 0; p < LPT; ++p) {
+        const u4v q = __builtin_amdgcn_raw_buffer_load_b128(rs, voff[p], 0, 0);
+        r[p] = make_uint4(q.x, q.y, q.z, q.w);
+      }
+    } else {
+      typedef unsigned Chunk __attribute__((ext_vector_type(4), aligned(2)));
+#pragma unroll
+      for (int p = 0; p < LPT; ++p) {
+        const Chunk q = *reinterpret_cast<const Chunk*>(reinterpret_cast<const char*>(base) + voff[p]);
+        r[p] = make_uint4(q.x, q.y, q.z, q.w);
+      }
     }
   }
 
@@ -196,12 +224,11 @@ struct Stager {
     }
   }
 
-  // whether a tile starting at (o0, k0) may use load_full
-  __device__ __forceinline__ static bool full_ok(const S* X, long ld, int o0, int Odim, int k0, int K) {
-    const bool in = (o0 + O <= Odim) && (k0 + BK <= K);
-    const bool al = ((reinterpret_cast<uintptr_t>(X) & 15) == 0) && (ld % VE == 0) &&
-                    (KC ? (k0 % VE == 0) : (o0 % VE == 0));
-    return in && al;
+  // whether the whole K tiles of a tile starting at outer element o0 may use
+  // load_full: chunks along K always, chunks along the outer index if all of
+  // the tile's are inside
+  __device__ __forceinline__ static bool full_ok(long ld, int o0, int Odim) {
+    return full_fits(ld) && (KC || o0 + O <= Odim);
   }
 
   __device__ __forceinline__ void store(S* __restrict__ s) const {

@@ -96,6 +96,9 @@ void op_apply_heff(Ctx* c, d3s_prec p, int ml, int d, int mr, int wl, int wr, co
   const size_t tsz = (p == D3S_F64) ? 8 : 4;       // T1 element size (fp32 for BF16 too)
   const size_t t2sz = (p == D3S_F64) ? 8 : (p == D3S_F32 ? 4 : 2);
   const size_t esz = t2sz;
+  // T1 and the copy of psi are needed only where the first two contractions
+  // are not fused; all three live in the workspace either way, so that a
+  // captured product never has to allocate
   void* T1 = ws_get(c, WS_T1, tsz * (size_t)ml * wl * d * mr);
   void* T2 = ws_get(c, WS_T2, t2sz * (size_t)ml * d * wr * mr);
   void* psiT = ws_get(c, WS_PSIT, esz * (size_t)ml * d * mr);
@@ -108,18 +111,23 @@ void heff_product(Ctx* c, d3s_prec p, int ml, int d, int mr, int wl, int wr, con
   hipEvent_t* ev = nullptr;
   if (!plain && c->prof && c->prof_n < c->prof_cap) ev = &c->prof_ev[4 * (size_t)c->prof_n++];
   if (ev) D3S_HIP(hipEventRecord(ev[0], c->stream));
-  // GEMM-1's B operand psi[x][(t,y)] runs along N; a copy psi^T[(t,y)][x]
-  // runs along K, which keeps the LDS staging of B in 16-byte vector stores
-  // (the transposing stores cost most in BF16).  Counted in GEMM-1's time.
-  const size_t esz = (p == D3S_F64) ? 8 : (p == D3S_F32 ? 4 : 2);
-  transpose_any(c, (int)esz, psi, ml, (long)d * mr, psiT);
-  GemmArgs g1{ml * wl, d * mr, ml, L, ml, true, 0, psiT, ml, true, 0, T1, (long)d * mr, 0, 1.0, 0.0, 1};
-  g1.part = part;
-  g1.part_cap = part_cap;
-  if (plain) gemm(c, p, g1);
-  else tuned_gemm(c, p, g1);
-  if (ev) D3S_HIP(hipEventRecord(ev[1], c->stream));
-  wmap_l2r(c, p, T1, W, T2, (long)wr * mr, ml, d, mr, wl, wr, 1.0);
+  if (front_wmap(c, p, D3S_L2R, ml, d, mr, wl, wr, L, W, psi, T2, (long)wr * mr, 1.0)) {
+    // GEMM-1 and the W-map in one launch: timed as GEMM-1
+    if (ev) D3S_HIP(hipEventRecord(ev[1], c->stream));
+  } else {
+    // GEMM-1's B operand psi[x][(t,y)] runs along N; a copy psi^T[(t,y)][x]
+    // runs along K, which keeps the LDS staging of B in 16-byte vector stores
+    // (the transposing stores cost most in BF16).  Counted in GEMM-1's time.
+    const size_t esz = (p == D3S_F64) ? 8 : (p == D3S_F32 ? 4 : 2);
+    transpose_any(c, (int)esz, psi, ml, (long)d * mr, psiT);
+    GemmArgs g1{ml * wl, d * mr, ml, L, ml, true, 0, psiT, ml, true, 0, T1, (long)d * mr, 0, 1.0, 0.0, 1};
+    g1.part = part;
+    g1.part_cap = part_cap;
+    if (plain) gemm(c, p, g1);
+    else tuned_gemm(c, p, g1);
+    if (ev) D3S_HIP(hipEventRecord(ev[1], c->stream));
+    wmap_l2r(c, p, T1, W, T2, (long)wr * mr, ml, d, mr, wl, wr, 1.0);
+  }
   if (ev) D3S_HIP(hipEventRecord(ev[2], c->stream));
   GemmArgs g2{ml * d, mr, wr * mr, T2, (long)wr * mr, true, 0, R, (long)wr * mr, true, 0, out, mr, 0,
               1.0, 0.0, 1};
@@ -172,18 +180,23 @@ void op_expand(Ctx* c, d3s_dir dir, int ml, int d, int mr, int wl, int wr, const
   if (dir == D3S_L2R) {
     // Mt = [psi | alpha L psi W]  ((ml d) x (mr + wr mr))
     const long ldm = (long)(1 + wr) * mr;
-    double* T1 = (double*)ws_get(c, WS_T1, sizeof(double) * (size_t)ml * wl * d * mr);
-    GemmArgs g1{ml * wl, d * mr, ml, env, ml, true, 0, psi, (long)d * mr, false, 0, T1, (long)d * mr, 0,
-                1.0, 0.0, 1};
-    gemm_f64(c, g1);
-    wmap_l2r(c, D3S_F64, T1, W, Mt + mr, ldm, ml, d, mr, wl, wr, alpha);
+    if (!front_wmap(c, D3S_F64, dir, ml, d, mr, wl, wr, env, W, psi, Mt + mr, ldm, alpha)) {
+      double* T1 = (double*)ws_get(c, WS_T1, sizeof(double) * (size_t)ml * wl * d * mr);
+      GemmArgs g1{ml * wl, d * mr, ml, env, ml, true, 0, psi, (long)d * mr, false, 0, T1, (long)d * mr, 0,
+                  1.0, 0.0, 1};
+      gemm_f64(c, g1);
+      wmap_l2r(c, D3S_F64, T1, W, Mt + mr, ldm, ml, d, mr, wl, wr, alpha);
+    }
     copy2d_f64(c, psi, mr, Mt, ldm, (long)ml * d, mr);
   } else {
     // Mt = [psi ; alpha W psi R]  ((ml + wl ml) x (d mr)); Y[(x,t),(b,v)] = psi R^T over y
-    double* Y = (double*)ws_get(c, WS_T1, sizeof(double) * (size_t)ml * d * mr * wr);
-    GemmArgs g1{ml * d, mr * wr, mr, psi, mr, true, 0, env, mr, true, 0, Y, (long)mr * wr, 0, 1.0, 0.0, 1};
-    gemm_f64(c, g1);
-    wmap_r2l(c, D3S_F64, Y, W, Mt + (long)ml * d * mr, ml, d, mr, wl, wr, alpha);
+    double* P = Mt + (long)ml * d * mr;
+    if (!front_wmap(c, D3S_F64, dir, ml, d, mr, wl, wr, env, W, psi, P, 0, alpha)) {
+      double* Y = (double*)ws_get(c, WS_T1, sizeof(double) * (size_t)ml * d * mr * wr);
+      GemmArgs g1{ml * d, mr * wr, mr, psi, mr, true, 0, env, mr, true, 0, Y, (long)mr * wr, 0, 1.0, 0.0, 1};
+      gemm_f64(c, g1);
+      wmap_r2l(c, D3S_F64, Y, W, P, ml, d, mr, wl, wr, alpha);
+    }
     copy_f64(c, psi, Mt, (long)ml * d * mr);
   }
 }
@@ -192,22 +205,26 @@ void op_expand(Ctx* c, d3s_dir dir, int ml, int d, int mr, int wl, int wr, const
 void op_update_env(Ctx* c, d3s_dir dir, int ml, int d, int mr, int wl, int wr, const double* env_in,
                    const double* W, const double* site, double* env_out) {
   if (dir == D3S_L2R) {
-    double* T1 = (double*)ws_get(c, WS_T1, sizeof(double) * (size_t)ml * wl * d * mr);
     double* T2 = (double*)ws_get(c, WS_T2, sizeof(double) * (size_t)ml * d * wr * mr);
-    GemmArgs g1{ml * wl, d * mr, ml, env_in, ml, true, 0, site, (long)d * mr, false, 0, T1, (long)d * mr, 0,
-                1.0, 0.0, 1};
-    gemm_f64(c, g1);
-    wmap_l2r(c, D3S_F64, T1, W, T2, (long)wr * mr, ml, d, mr, wl, wr, 1.0);
+    if (!front_wmap(c, D3S_F64, dir, ml, d, mr, wl, wr, env_in, W, site, T2, (long)wr * mr, 1.0)) {
+      double* T1 = (double*)ws_get(c, WS_T1, sizeof(double) * (size_t)ml * wl * d * mr);
+      GemmArgs g1{ml * wl, d * mr, ml, env_in, ml, true, 0, site, (long)d * mr, false, 0, T1, (long)d * mr, 0,
+                  1.0, 0.0, 1};
+      gemm_f64(c, g1);
+      wmap_l2r(c, D3S_F64, T1, W, T2, (long)wr * mr, ml, d, mr, wl, wr, 1.0);
+    }
     // env_out[b][(v,y)] = sum_{(a,s)} A[(a,s)][b] T2[(a,s)][(v,y)]
     GemmArgs g2{mr, wr * mr, ml * d, site, mr, false, 0, T2, (long)wr * mr, false, 0, env_out,
                 (long)wr * mr, 0, 1.0, 0.0, 1};
     gemm_f64(c, g2);
   } else {
-    double* Y = (double*)ws_get(c, WS_T1, sizeof(double) * (size_t)ml * d * mr * wr);
     double* Z = (double*)ws_get(c, WS_T2, sizeof(double) * (size_t)wl * ml * d * mr);
-    GemmArgs g1{ml * d, mr * wr, mr, site, mr, true, 0, env_in, mr, true, 0, Y, (long)mr * wr, 0, 1.0, 0.0, 1};
-    gemm_f64(c, g1);
-    wmap_r2l(c, D3S_F64, Y, W, Z, ml, d, mr, wl, wr, 1.0);
+    if (!front_wmap(c, D3S_F64, dir, ml, d, mr, wl, wr, env_in, W, site, Z, 0, 1.0)) {
+      double* Y = (double*)ws_get(c, WS_T1, sizeof(double) * (size_t)ml * d * mr * wr);
+      GemmArgs g1{ml * d, mr * wr, mr, site, mr, true, 0, env_in, mr, true, 0, Y, (long)mr * wr, 0, 1.0, 0.0, 1};
+      gemm_f64(c, g1);
+      wmap_r2l(c, D3S_F64, Y, W, Z, ml, d, mr, wl, wr, 1.0);
+    }
     // env_out[a][(w,x)] = sum_{(s,b)} B[a][(s,b)] Z[(w,x)][(s,b)]
     GemmArgs g2{ml, wl * ml, d * mr, site, (long)d * mr, true, 0, Z, (long)d * mr, true, 0, env_out,
                 (long)wl * ml, 0, 1.0, 0.0, 1};

@@ -1,0 +1,113 @@
+"""Products on wave tiles (csrc/direct.hip) and on unaligned workgroup tiles,
+against the dense FP64 oracle, at the sizes where their tiles and K steps end:
+bonds one below, at and one above a K step (16 doubles, 32 floats) and a tile,
+one K step or less, MPO bonds that do and do not divide a tile's rows, physical
+dimensions with and without the fused W-map.
+
+Tolerances: FP64 1e-12 and FP32 3e-5 of the largest entry, as in
+test_gpu_parity (about sqrt(K) u for the longest sums here, K <= 8192)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import contract as C
+from paper_1501_05504_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+abi = pytest.importorskip("paper_1501_05504_amd.abi")
+
+DEV = torch.device("cuda:0")
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = abi.Context(0)
+    yield c
+    c.close()
+
+
+def rel(got, ref):
+    return float(np.abs(got - ref).max() / np.abs(ref).max())
+
+
+def inputs(ml, d, mr, wl, wr, dt):
+    g = [synth.gaussian(s, 900 + i) for i, s in enumerate([(ml, wl, ml), (wl, wr, d, d), (mr, wr, mr), (ml, d, mr)])]
+    if dt == torch.float32:
+        g = [x.astype(np.float32).astype(np.float64) for x in g]
+    return g, [torch.tensor(x, dtype=dt, device=DEV) for x in g]
+
+
+SHAPES = [(1, 2, 1, 1, 1), (15, 4, 16, 6, 6), (16, 4, 17, 6, 6), (17, 2, 15, 5, 5), (31, 4, 33, 6, 6),
+          (33, 2, 31, 8, 8), (32, 4, 32, 1, 6), (40, 4, 64, 6, 1), (65, 2, 63, 40, 7), (9, 4, 70, 18, 18),
+          (34, 3, 21, 5, 5), (50, 2, 47, 17, 3), (129, 4, 127, 6, 6), (257, 4, 255, 6, 6), (513, 2, 700, 5, 5)]
+
+
+@pytest.mark.parametrize("dt", [torch.float64, torch.float32], ids=["f64", "f32"])
+@pytest.mark.parametrize("shape", SHAPES, ids=["-".join(map(str, s)) for s in SHAPES])
+def test_heff_at_tile_edges(ctx, shape, dt):
+    ml, d, mr, wl, wr = shape
+    (L, W, R, psi), t = inputs(ml, d, mr, wl, wr, dt)
+    out = torch.full((ml, d, mr), float("nan"), dtype=dt, device=DEV)
+    ctx.apply_heff(*t, out)
+    torch.cuda.synchronize()
+    assert rel(out.cpu().double().numpy(), C.apply_heff(L, W, R, psi)) < (1e-12 if dt == torch.float64 else 3e-5)
+
+
+@pytest.mark.parametrize("direction", ["l2r", "r2l"])
+@pytest.mark.parametrize("shape", SHAPES[:13], ids=["-".join(map(str, s)) for s in SHAPES[:13]])
+def test_expansion_and_environment_at_tile_edges(ctx, shape, direction):
+    ml, d, mr, wl, wr = shape
+    (L, W, R, psi), (tL, tW, tR, tpsi) = inputs(ml, d, mr, wl, wr, torch.float64)
+    if direction == "l2r":
+        T = np.einsum("awx,xty->awty", L, psi)
+        T2 = np.einsum("wvst,awty->asvy", W, T)
+        mt = np.concatenate([psi.reshape(ml * d, mr), 0.5 * T2.reshape(ml * d, wr * mr)], 1)
+        env = np.einsum("asb,asvy->bvy", psi, T2)
+        args = (abi.L2R, tL)
+    else:
+        Y = np.einsum("xty,bvy->xtbv", psi, R)
+        Z = np.einsum("wvst,xtbv->wxsb", W, Y)
+        mt = np.concatenate([psi.reshape(ml, d * mr), 0.5 * Z.reshape(wl * ml, d * mr)], 0)
+        env = np.einsum("asb,wxsb->awx", psi, Z)
+        args = (abi.R2L, tR)
+    Mt = torch.full(mt.shape, float("nan"), dtype=torch.float64, device=DEV)
+    ctx.expand_subspace(args[0], args[1], tW, tpsi, 0.5, Mt)
+    out = torch.full(env.shape, float("nan"), dtype=torch.float64, device=DEV)
+    ctx.update_env(args[0], args[1], tW, tpsi, out)
+    torch.cuda.synchronize()
+    assert rel(Mt.cpu().numpy(), mt) < 1e-12
+    assert rel(out.cpu().numpy(), env) < 1e-12
+
+
+@pytest.mark.parametrize("dt", [torch.float64, torch.float32], ids=["f64", "f32"])
+@pytest.mark.parametrize("mlp,mr,wr", [(33, 1, 6), (70, 1030, 8), (520, 65, 2), (1030, 1028, 2)])
+def test_long_and_large_products(ctx, mlp, mr, wr, dt):
+    """Two plain GEMMs (the centre-matrix application): sums long enough to be
+    split over the grid, and sizes on both sides of the wave-tile rule."""
+    g = [synth.gaussian(s, 950 + i) for i, s in enumerate([(mlp, wr, mlp), (mr, wr, mr), (mlp, mr)])]
+    if dt == torch.float32:
+        g = [x.astype(np.float32).astype(np.float64) for x in g]
+    Lt, R, Cm = [torch.tensor(x, dtype=dt, device=DEV) for x in g]
+    out = torch.full((mlp, mr), float("nan"), dtype=dt, device=DEV)
+    ctx.apply_cwf(Lt, R, Cm, out)
+    torch.cuda.synchronize()
+    T = np.tensordot(g[0], g[2], axes=([2], [0]))
+    ref = np.tensordot(T, g[1], axes=([1, 2], [1, 2]))
+    assert rel(out.cpu().double().numpy(), ref) < (1e-12 if dt == torch.float64 else 3e-5)
+
+
+def test_infinite_entry_stays_in_its_rows(ctx):
+    """An Inf in one row of L reaches only that row's outputs, also where the
+    last K step is not whole and tiles are padded."""
+    ml, d, mr, w = 37, 4, 29, 6
+    (L, W, R, psi), (tL, tW, tR, tpsi) = inputs(ml, d, mr, w, w, torch.float64)
+    tL[5, 2, 36] = float("inf")
+    out = torch.empty((ml, d, mr), dtype=torch.float64, device=DEV)
+    ctx.apply_heff(tL, tW, tR, tpsi, out)
+    torch.cuda.synchronize()
+    o = out.cpu().numpy()
+    ref = C.apply_heff(L, W, R, psi)
+    keep = np.arange(ml) != 5
+    assert not np.isfinite(o[5]).any()
+    assert rel(o[keep], ref[keep]) < 1e-12
