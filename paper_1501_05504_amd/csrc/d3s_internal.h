@@ -212,30 +212,30 @@ void wmap_blocks(Ctx* c, d3s_prec p, const void* in, const void* W, void* out, c
 
 // deterministic reductions (FP64)
 void dot_f64(Ctx* c, const double* x, const double* y, long n, double* out_dev);
-// coef[j] = <V_j, w> for j < k, V rows of length n with stride ldv.  With
-// kdev the row count is *kdev + 1 (read on the device; k is then the
-// largest possible count), so one captured launch serves every step.
-void mdot_f64(Ctx* c, const double* V, long ldv, int k, const double* w, long n, double* coef_dev,
-              const int* kdev = nullptr);
-// partial-sum count of the Gram-Schmidt kernels for vectors of length n (fixed by n)
+// coef[j] = <V_j, w> for j < k <= 128, V rows of length n with stride ldv
+void mdot_f64(Ctx* c, const double* V, long ldv, int k, const double* w, long n, double* coef_dev);
 // partial sums per Gram-Schmidt pass: one per workgroup, at most kGsMaxBlocks
 constexpr int kGsMaxBlocks = 1024;
 int gs_blocks(long n);
-// fused second pass: w -= sum_j coef1_j V_j, then coef2 = V^T w (rows k or *kdev + 1, <= 64)
-void gs_second_pass(Ctx* c, const double* V, long ldv, int k, const int* kdev, const double* coef1, double* w,
-                    long n, double* coef2);
-// w -= sum_j coef_j V_j with the per-block partials of |w|^2 in npart (gs_blocks(n) entries)
-void gs_update_norm(Ctx* c, const double* V, long ldv, int k, const int* kdev, const double* coef, double* w,
-                    long n, double* npart);
+// at most this many partial sums a row are summed by the pass that needs them
+// (four per lane of a wave)
+constexpr int kGsFused = 256;
+// Classical Gram-Schmidt of w twice against the rows V_j (k or *kdev + 1 of
+// them, <= 64; with kdev, k is the largest possible count): coef1, coef2 the
+// coefficients of the two passes, npart the per-block partials of the final
+// |w|^2 (gs_blocks(n) entries); *knext = the row count (may be null).
+void gram_schmidt(Ctx* c, const double* V, long ldv, int k, const int* kdev, double* w, long n, double* coef1,
+                  double* coef2, double* npart, int* knext);
 // Lanczos step end (k from the host, or *kdev): beta = sqrt(sum of npart), V_{k+1} = w / beta
-// unless k+1 = kk; ab[2k] = c1[k] + c2[k], ab[2k+1] = beta
+// unless k+1 = kk; ab[2k] = c1[k] + c2[k], ab[2k+1] = beta (device or pinned host memory)
 void lanczos_tail(Ctx* c, const double* w, long n, const double* npart, const double* c1, const double* c2, int k,
                   const int* kdev, int kk, double* V, double* ab);
-void copy_row_f64(Ctx* c, const double* V, long n, const int* kdev, double* dst);   // dst = V_{*kdev}
-void set_int_dev(Ctx* c, int* p, int v, bool add);                                   // *p = v or *p += v
-// w += sign * sum_j coef[j] V_j  (coef on device; row count k or *kdev + 1)
+// dst = V_k, *kcur = k with k = *knext
+void copy_row_f64(Ctx* c, const double* V, long n, const int* knext, int* kcur, double* dst);
+void set_int_dev(Ctx* c, int* p, int v);                                             // *p = v
+// w = sign * sum_j coef[j] V_j (+ w when accumulate; coef on device; row count k or *kdev + 1)
 void maxpy_f64(Ctx* c, const double* V, long ldv, int k, const double* coef_dev, double sign,
-               double* w, long n, const int* kdev = nullptr);
+               double* w, long n, const int* kdev = nullptr, bool accumulate = true);
 void scale_f64(Ctx* c, double* x, long n, double s_host);
 void scale_by_dev_f64(Ctx* c, double* x, long n, const double* s_dev, bool reciprocal);
 void axpby_f64(Ctx* c, double a, const double* x, double b, double* y, long n);

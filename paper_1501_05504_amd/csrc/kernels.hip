@@ -394,180 +394,200 @@ void dot_partial_kernel(const double* __restrict__ x, const double* __restrict__
   if (threadIdx.x == 0) part[blockIdx.x] = s;
 }
 
-// coef-partials for up to KMAX rows at once: each thread keeps one running
-// sum per row over its grid-stride elements (w is read once), then every row
-// is reduced over the block; part[j * gridDim.x + block].
-// The row count of a Lanczos step is read from device memory, so the kernels
-// below branch once, uniformly, to a body compiled for the next multiple of
-// eight rows (rows past the last one are clamped to it and weighted by
-// zero): every load of an element's rows is issued without a test, so a
-// wave keeps many loads in flight.
+// Sums over a wave of R running sums per lane at once: at every step a lane
+// hands half of its rows to its partner and adds the partner's half of the
+// others, so R rows take R - 1 exchanges (+ one per further step) instead of
+// 6 R.  Returns the total of row `lane / (64 / P)`, P the power of two >= R;
+// the order of the additions is fixed.
+template <int R> constexpr int pow2_rows() { return R <= 8 ? 8 : R <= 16 ? 16 : R <= 32 ? 32 : 64; }
 template <int R>
-__device__ __forceinline__ void mdot_rows(const double* __restrict__ Vj, long ldv, int kc,
-                                          const double* __restrict__ w, long n, double* acc) {
-  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) {
-    const double wi = w[i];
+__device__ __forceinline__ double wave_row_sums(const double* acc) {
+  constexpr int P = pow2_rows<R>();
+  const int lane = threadIdx.x & 63;
+  double v[P];
 #pragma unroll
-    for (int j = 0; j < R; ++j) acc[j] += Vj[(long)min(j, kc - 1) * ldv + i] * wi;
-  }
-}
-
-template <int KMAX>
-__global__ __launch_bounds__(kThreads, 2)
-void mdot_partial_kernel(const double* __restrict__ V, long ldv, int k, const int* __restrict__ kdev, int j0,
-                         const double* __restrict__ w, long n, double* __restrict__ part) {
-  __shared__ double sh[kThreads / 64][KMAX];
-  // rows of this launch: j0 .. j0 + kc - 1 of the k (or *kdev + 1) rows
-  const int rows = kdev ? (*kdev + 1) : k;
-  const int kc = min(rows - j0, KMAX);
-  if (kc <= 0) return;
-  const double* Vj = V + (long)j0 * ldv;
-  double acc[KMAX];
+  for (int j = 0; j < P; ++j) v[j] = j < R ? acc[j] : 0.0;
 #pragma unroll
-  for (int j = 0; j < KMAX; ++j) acc[j] = 0.0;
-  switch ((kc + 7) / 8) {
-    case 1: mdot_rows<(KMAX < 8 ? KMAX : 8)>(Vj, ldv, kc, w, n, acc); break;
-    case 2: if constexpr (KMAX >= 16) mdot_rows<16>(Vj, ldv, kc, w, n, acc); break;
-    case 3: if constexpr (KMAX >= 24) mdot_rows<24>(Vj, ldv, kc, w, n, acc); break;
-    case 4: if constexpr (KMAX >= 32) mdot_rows<32>(Vj, ldv, kc, w, n, acc); break;
-    case 5: if constexpr (KMAX >= 40) mdot_rows<40>(Vj, ldv, kc, w, n, acc); break;
-    case 6: if constexpr (KMAX >= 48) mdot_rows<48>(Vj, ldv, kc, w, n, acc); break;
-    case 7: if constexpr (KMAX >= 56) mdot_rows<56>(Vj, ldv, kc, w, n, acc); break;
-    default: if constexpr (KMAX >= 64) mdot_rows<64>(Vj, ldv, kc, w, n, acc); break;
-  }
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int h = P / 2, off = 32; off > 0; h /= 2, off /= 2) {
+    if (h > 0) {
+      const bool up = (lane & off) != 0;
 #pragma unroll
-  for (int j = 0; j < KMAX; ++j) {
-    if (j < kc) {
-      double v = acc[j];
-      for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-      if (lane == 0) sh[wave][j] = v;
-    }
-  }
-  __syncthreads();
-  for (int j = threadIdx.x; j < kc; j += blockDim.x) {
-    double t = 0.0;
-    for (int q = 0; q < (int)(blockDim.x >> 6); ++q) t += sh[q][j];
-    part[(long)(j0 + j) * gridDim.x + blockIdx.x] = t;
-  }
-}
-
-// Second Gram-Schmidt pass fused with the first one's update: with
-// c = -coef (the first pass's coefficients), w <- w + sum_j c_j V_j, and the
-// partial sums of <V_j, w_new> for the second pass, reading every V_j once.
-template <int R>
-__device__ __forceinline__ void gs_update_dot_rows(const double* __restrict__ V, long ldv, int rows,
-                                                   const double* sc, double* __restrict__ w, long n,
-                                                   double* acc) {
-  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) {
-    double v[R];
-    double x = w[i];
-#pragma unroll
-    for (int j = 0; j < R; ++j) {
-      v[j] = V[(long)min(j, rows - 1) * ldv + i];
-      x += sc[j] * v[j];
-    }
-    w[i] = x;
-#pragma unroll
-    for (int j = 0; j < R; ++j) acc[j] += v[j] * x;
-  }
-}
-
-template <int KMAX>
-__global__ __launch_bounds__(kThreads, 2)
-void gs_update_dot_kernel(const double* __restrict__ V, long ldv, int k, const int* __restrict__ kdev,
-                          const double* __restrict__ coef, double* __restrict__ w, long n,
-                          double* __restrict__ part) {
-  __shared__ double sc[KMAX];
-  __shared__ double sh[kThreads / 64][KMAX];
-  const int rows = kdev ? (*kdev + 1) : k;
-  for (int j = threadIdx.x; j < KMAX; j += blockDim.x) sc[j] = (j < rows) ? -coef[j] : 0.0;
-  __syncthreads();
-  double acc[KMAX];
-#pragma unroll
-  for (int j = 0; j < KMAX; ++j) acc[j] = 0.0;
-  switch ((rows + 7) / 8) {
-    case 1: gs_update_dot_rows<8>(V, ldv, rows, sc, w, n, acc); break;
-    case 2: gs_update_dot_rows<16>(V, ldv, rows, sc, w, n, acc); break;
-    case 3: if constexpr (KMAX >= 24) gs_update_dot_rows<24>(V, ldv, rows, sc, w, n, acc); break;
-    case 4: if constexpr (KMAX >= 32) gs_update_dot_rows<32>(V, ldv, rows, sc, w, n, acc); break;
-    case 5: if constexpr (KMAX >= 40) gs_update_dot_rows<40>(V, ldv, rows, sc, w, n, acc); break;
-    case 6: if constexpr (KMAX >= 48) gs_update_dot_rows<48>(V, ldv, rows, sc, w, n, acc); break;
-    case 7: if constexpr (KMAX >= 56) gs_update_dot_rows<56>(V, ldv, rows, sc, w, n, acc); break;
-    default: if constexpr (KMAX >= 64) gs_update_dot_rows<64>(V, ldv, rows, sc, w, n, acc); break;
-  }
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int j = 0; j < KMAX; ++j) {
-    if (j < rows) {
-      double t = acc[j];
-      for (int off = 32; off > 0; off >>= 1) t += __shfl_down(t, off, 64);
-      if (lane == 0) sh[wave][j] = t;
-    }
-  }
-  __syncthreads();
-  for (int j = threadIdx.x; j < rows; j += blockDim.x) {
-    double t = 0.0;
-    for (int q = 0; q < (int)(blockDim.x >> 6); ++q) t += sh[q][j];
-    part[(long)j * gridDim.x + blockIdx.x] = t;
-  }
-}
-
-// Second pass update fused with the norm: w <- w - sum_j coef_j V_j and the
-// per-block partial sums of |w_new|^2 (part[block]).
-__global__ __launch_bounds__(kThreads, 2)
-void gs_update_norm_kernel(const double* __restrict__ V, long ldv, int k, const int* __restrict__ kdev,
-                           const double* __restrict__ coef, double* __restrict__ w, long n,
-                           double* __restrict__ part) {
-  __shared__ double sc[128];
-  __shared__ double sh[kThreads / 64];
-  const int rows = kdev ? (*kdev + 1) : k;
-  for (int j = threadIdx.x; j < 128; j += blockDim.x) sc[j] = (j < rows) ? -coef[j] : 0.0;
-  __syncthreads();
-  double acc = 0.0;
-  // rows in chunks of 8 (runtime count R/8): loads within a chunk are
-  // issued together, and the register use stays bounded for any R
-  auto pass = [&](auto rt) {
-    constexpr int R = decltype(rt)::value;
-    for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) {
-      double x = w[i];
-#pragma unroll 2
-      for (int jc = 0; jc < R; jc += 8) {
-        double v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = V[(long)min(jc + u, rows - 1) * ldv + i];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) x += sc[jc + u] * v[u];
+      for (int j = 0; j < h; ++j) {
+        const double mine = up ? v[j + h] : v[j], give = up ? v[j] : v[j + h];
+        v[j] = mine + __shfl_xor(give, off, 64);
       }
-      w[i] = x;
-      acc += x * x;
+    } else {
+      v[0] += __shfl_xor(v[0], off, 64);
     }
+  }
+  return v[0];
+}
+
+// sc[j] = -(the coefficient of row j), zero for rows <= j < 4 RW: read from
+// coef, or (cpart given) summed here from the nbp partial sums of every row,
+// by every workgroup in the same order, the first one storing them to coef.
+// A wave takes the rows wave, wave + 4, ... and has all their partial sums in
+// flight at once.  Ends with a barrier.
+template <int RW>
+__device__ __forceinline__ void load_coefs(double* sc, int rows, double* coef, const double* __restrict__ cpart,
+                                           int nbp) {
+  if (cpart && nbp <= 16) {
+    // short rows: four lanes a row
+    const int q = threadIdx.x & 3, j = threadIdx.x >> 2;
+    if (j < 4 * RW) {
+      const double* p = cpart + (long)min(j, rows - 1) * nbp;
+      double u[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) u[i] = (q + 4 * i < nbp) ? p[q + 4 * i] : 0.0;
+      double t = (u[0] + u[1]) + (u[2] + u[3]);
+      t += __shfl_xor(t, 1, 64);
+      t += __shfl_xor(t, 2, 64);
+      if (q == 0) {
+        sc[j] = (j < rows) ? -t : 0.0;
+        if (blockIdx.x == 0 && j < rows) coef[j] = t;
+      }
+    }
+  } else if (cpart) {
+    constexpr int W = 64 / pow2_rows<RW>();
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    double acc[RW];
+#pragma unroll
+    for (int j = 0; j < RW; ++j) {
+      const double* p = cpart + (long)min(wave + 4 * j, rows - 1) * nbp;
+      double t[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) t[u] = (lane + 64 * u < nbp) ? p[lane + 64 * u] : 0.0;
+      acc[j] = (t[0] + t[1]) + (t[2] + t[3]);
+    }
+    const double t = wave_row_sums<RW>(acc);
+    const int r = wave + 4 * (lane / W);
+    if (lane % W == 0 && lane / W < RW) {
+      sc[r] = (r < rows) ? -t : 0.0;
+      if (blockIdx.x == 0 && r < rows) coef[r] = t;
+    }
+  } else {
+    for (int j = threadIdx.x; j < 4 * RW; j += blockDim.x) sc[j] = (j < rows) ? -coef[j] : 0.0;
+  }
+  __syncthreads();
+}
+
+// One pass of Gram-Schmidt over at most 64 rows of V, kGsChunk elements of
+// every row per workgroup and turn:
+//   MODE 0: the partial sums of <V_j, w>
+//   MODE 1: w <- w + sum_j sc_j V_j (sc = -coefficients) and the partial sums
+//           of <V_j, w_new>
+//   MODE 2: the same update and the partial sum of |w_new|^2
+// The rows are dealt to the four waves; a wave holds its (at most 16) rows of
+// the chunk in registers, four consecutive elements a lane, so V is read once
+// in 16-byte loads that are all in flight together, and the update's four
+// shares meet in LDS.  The row count may be read from device memory, so the
+// kernel branches once, uniformly, to a body compiled for the rows a wave has
+// (rows past the last one are clamped to it and weighted by zero).  Bound by
+// the latency of one turn for short vectors and by L2 / HBM for long ones.
+// Measured, MODE 0 / 1 / 2, about 20 rows: n = 61440 4.2 / 6.7 / 5.8 us (a
+// thread per element with all rows in every wave, 64 workgroups: 15 / 12 / 8.5
+// us and two launches of 4 us for the sums), n = 2048 3.5 / 4.3 / 3.4 us (8.2 /
+// 8.2 / 4.4 us and the two launches).
+constexpr int kGsChunk = kThreads;
+typedef double d2u __attribute__((ext_vector_type(2), aligned(8)));
+
+template <int MODE, int RW>
+__device__ __forceinline__ void gs_pass_rows(const double* __restrict__ V, long ldv, int rows, const double* sc,
+                                             double (*sx)[kGsChunk], double* __restrict__ w, long n,
+                                             double* __restrict__ part) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  double acc[RW];
+#pragma unroll
+  for (int j = 0; j < RW; ++j) acc[j] = 0.0;
+  const long chunks = (n + kGsChunk - 1) / kGsChunk;
+  for (long ch = blockIdx.x; ch < chunks; ch += gridDim.x) {
+    const long i0 = ch * kGsChunk + lane * 4;
+    const bool whole = (ch + 1) * kGsChunk <= n;
+    auto load4 = [&](const double* p, double (&v)[4]) {
+      if (whole) {
+        const d2u a = *reinterpret_cast<const d2u*>(p + i0), b = *reinterpret_cast<const d2u*>(p + i0 + 2);
+        v[0] = a.x; v[1] = a.y; v[2] = b.x; v[3] = b.y;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = (i0 + e < n) ? p[i0 + e] : 0.0;
+      }
+    };
+    double x[4], v[RW][4];
+    load4(w, x);
+#pragma unroll
+    for (int j = 0; j < RW; ++j) load4(V + (long)min(wave + 4 * j, rows - 1) * ldv, v[j]);
+    if constexpr (MODE > 0) {
+      double u[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int j = 0; j < RW; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) u[e] += sc[wave + 4 * j] * v[j][e];
+      __syncthreads();                   // the previous turn's shares have been read
+#pragma unroll
+      for (int e = 0; e < 4; ++e) sx[wave][lane * 4 + e] = u[e];
+      __syncthreads();                   // ... and every wave has loaded w
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        x[e] += (sx[0][lane * 4 + e] + sx[1][lane * 4 + e]) + (sx[2][lane * 4 + e] + sx[3][lane * 4 + e]);
+      if (wave == 0) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (i0 + e < n) w[i0 + e] = x[e];
+      }
+    }
+    if constexpr (MODE < 2) {
+#pragma unroll
+      for (int j = 0; j < RW; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[j] += v[j][e] * x[e];
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[0] += x[e] * x[e];
+    }
+  }
+  if constexpr (MODE < 2) {
+    constexpr int W = 64 / pow2_rows<RW>();
+    const double t = wave_row_sums<RW>(acc);
+    const int r = wave + 4 * (lane / W);
+    if (lane % W == 0 && lane / W < RW && r < rows) part[(long)r * gridDim.x + blockIdx.x] = t;
+  } else {
+    double t = acc[0];
+    for (int off = 32; off > 0; off >>= 1) t += __shfl_down(t, off, 64);
+    if (threadIdx.x == 0) part[blockIdx.x] = t;
+  }
+}
+
+template <int MODE>
+__global__ __launch_bounds__(kThreads, 2)
+void gs_pass_kernel(const double* __restrict__ V, long ldv, int k, const int* __restrict__ kdev,
+                    double* __restrict__ coef, const double* __restrict__ cpart, int nbp, double* __restrict__ w,
+                    long n, double* __restrict__ part, int* __restrict__ knext) {
+  __shared__ double sc[64];
+  __shared__ double sx[4][kGsChunk];
+  const int rows = kdev ? (*kdev + 1) : k;
+  // the next step's index: nothing in this step reads it
+  if (knext && blockIdx.x == 0 && threadIdx.x == 0) *knext = rows;
+  auto go = [&](auto rt) {
+    constexpr int RW = decltype(rt)::value;
+    if constexpr (MODE > 0) load_coefs<RW>(sc, rows, coef, cpart, nbp);
+    gs_pass_rows<MODE, RW>(V, ldv, rows, sc, sx, w, n, part);
   };
   switch ((rows + 7) / 8) {
-    case 1: pass(std::integral_constant<int, 8>()); break;
-    case 2: pass(std::integral_constant<int, 16>()); break;
-    case 3: pass(std::integral_constant<int, 24>()); break;
-    case 4: pass(std::integral_constant<int, 32>()); break;
-    case 5: pass(std::integral_constant<int, 40>()); break;
-    case 6: pass(std::integral_constant<int, 48>()); break;
-    case 7: pass(std::integral_constant<int, 56>()); break;
-    case 8: pass(std::integral_constant<int, 64>()); break;
-    default:
-      for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) {
-        double x = w[i];
-        for (int j = 0; j < rows; ++j) x += sc[j] * V[(long)j * ldv + i];
-        w[i] = x;
-        acc += x * x;
-      }
+    case 1: go(std::integral_constant<int, 2>()); break;
+    case 2: go(std::integral_constant<int, 4>()); break;
+    case 3: go(std::integral_constant<int, 6>()); break;
+    case 4: go(std::integral_constant<int, 8>()); break;
+    case 5: go(std::integral_constant<int, 10>()); break;
+    case 6: go(std::integral_constant<int, 12>()); break;
+    case 7: go(std::integral_constant<int, 14>()); break;
+    default: go(std::integral_constant<int, 16>()); break;
   }
-  const double t = block_sum(acc, sh);
-  if (threadIdx.x == 0) part[blockIdx.x] = t;
 }
 
 // End of a Lanczos step k (k from the host, or *kdev): V_{k+1} = w / beta
 // with beta = sqrt(|w|^2) (zero when beta is not positive; skipped when
 // k+1 = kk), and ab[2k] = alpha_k (the projections of both Gram-Schmidt
-// passes on V_k), ab[2k+1] = beta.
+// passes on V_k), ab[2k+1] = beta (ab may be pinned host memory).
 __global__ __launch_bounds__(kThreads)
 void lanczos_tail_kernel(const double* __restrict__ w, long n, const double* __restrict__ npart, int nnp,
                          const double* __restrict__ c1, const double* __restrict__ c2, int k,
@@ -593,17 +613,19 @@ void lanczos_tail_kernel(const double* __restrict__ w, long n, const double* __r
     vnext[i] = w[i] * f;
 }
 
-// dst = V_{*kdev}
+// dst = V_k and *kcur = k, k = *knext
 __global__ __launch_bounds__(kThreads)
-void copy_row_kernel(const double* __restrict__ V, long n, const int* __restrict__ kdev, double* __restrict__ dst) {
-  const double* src = V + (long)(*kdev) * n;
+void copy_row_kernel(const double* __restrict__ V, long n, const int* __restrict__ knext, int* __restrict__ kcur,
+                     double* __restrict__ dst) {
+  const int k = *knext;
+  if (blockIdx.x == 0 && threadIdx.x == 0) *kcur = k;
+  const double* src = V + (long)k * n;
   for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x)
     dst[i] = src[i];
 }
 
-// *p = v, or *p += v
-__global__ void set_int_kernel(int* p, int v, int add) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) *p = add ? (*p + v) : v;
+__global__ void set_int_kernel(int* p, int v) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) *p = v;
 }
 
 // out[j] = sum_b part[j * nb + b] in a fixed order; one block per j
@@ -621,13 +643,13 @@ void reduce_rows_kernel(const double* __restrict__ part, int nb, double* __restr
 
 __global__ __launch_bounds__(kThreads)
 void maxpy_kernel(const double* __restrict__ V, long ldv, int k, const int* __restrict__ kdev,
-                  const double* __restrict__ coef, double sign, double* __restrict__ w, long n) {
+                  const double* __restrict__ coef, double sign, double* __restrict__ w, long n, int accumulate) {
   __shared__ double sc[128];
   if (kdev) k = *kdev + 1;
   for (int j = threadIdx.x; j < k; j += blockDim.x) sc[j] = sign * coef[j];
   __syncthreads();
   for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) {
-    double acc = w[i];
+    double acc = accumulate ? w[i] : 0.0;
     for (int j = 0; j < k; ++j) acc += sc[j] * V[(long)j * ldv + i];
     w[i] = acc;
   }
@@ -814,55 +836,49 @@ void dot_f64(Ctx* c, const double* x, const double* y, long n, double* out_dev) 
   D3S_HIP(hipGetLastError());
 }
 
-void mdot_f64(Ctx* c, const double* V, long ldv, int k, const double* w, long n, double* coef_dev,
-              const int* kdev) {
+void mdot_f64(Ctx* c, const double* V, long ldv, int k, const double* w, long n, double* coef_dev) {
   if (k <= 0) return;
   if (k > 128) throw Error{D3S_EINVAL, "mdot: more than 128 vectors"};
   // partial count fixed by n (deterministic), at most kGsMaxBlocks
   const int nb = gs_blocks(n);
   double* part = (double*)ws_get(c, WS_RED, sizeof(double) * (size_t)nb * 128);
-  for (int j0 = 0; j0 < k; j0 += 64) {
-    const int kc = std::min(64, k - j0);
-    auto go = [&](auto kern) {
-      hipLaunchKernelGGL(kern, dim3(nb), dim3(kThreads), 0, c->stream, V, ldv, k, kdev, j0, w, n, part);
-    };
-    if (kc <= 8) go(mdot_partial_kernel<8>);
-    else if (kc <= 16) go(mdot_partial_kernel<16>);
-    else if (kc <= 32) go(mdot_partial_kernel<32>);
-    else go(mdot_partial_kernel<64>);
-  }
-  hipLaunchKernelGGL(reduce_rows_kernel, dim3(k), dim3(kThreads), 0, c->stream, part, nb, coef_dev, kdev);
+  for (int j0 = 0; j0 < k; j0 += 64)
+    hipLaunchKernelGGL(gs_pass_kernel<0>, dim3(nb), dim3(kThreads), 0, c->stream, V + (long)j0 * ldv, ldv,
+                       std::min(64, k - j0), (const int*)nullptr, (double*)nullptr, (const double*)nullptr, 0,
+                       const_cast<double*>(w), n, part + (size_t)j0 * nb, (int*)nullptr);
+  hipLaunchKernelGGL(reduce_rows_kernel, dim3(k), dim3(kThreads), 0, c->stream, part, nb, coef_dev,
+                     (const int*)nullptr);
   D3S_HIP(hipGetLastError());
 }
 
 int gs_blocks(long n) {
-  return (int)std::max<long>(1, std::min<long>(kGsMaxBlocks, (n + 4L * kThreads - 1) / (4L * kThreads)));
+  return (int)std::max<long>(1, std::min<long>(kGsMaxBlocks, (n + kGsChunk - 1) / kGsChunk));
 }
 
-void gs_second_pass(Ctx* c, const double* V, long ldv, int k, const int* kdev, const double* coef1, double* w,
-                    long n, double* coef2) {
+void gram_schmidt(Ctx* c, const double* V, long ldv, int k, const int* kdev, double* w, long n, double* coef1,
+                  double* coef2, double* npart, int* knext) {
   if (k <= 0) return;
   if (k > 64) throw Error{D3S_EINVAL, "Gram-Schmidt: more than 64 vectors in the fused pass"};
   const int nb = gs_blocks(n);
-  double* part = (double*)ws_get(c, WS_RED, sizeof(double) * (size_t)nb * 128);
-  auto go = [&](auto kern) {
-    hipLaunchKernelGGL(kern, dim3(nb), dim3(kThreads), 0, c->stream, V, ldv, k, kdev, coef1, w, n, part);
+  // Up to kGsFused partial sums a row every workgroup of the next pass adds
+  // them up itself, which costs it a few loads per thread; beyond, a launch
+  // between the passes does (about 4 us)
+  const bool fused = nb <= kGsFused;
+  double* p1 = (double*)ws_get(c, WS_RED, sizeof(double) * (size_t)nb * 128);
+  double* p2 = p1 + (size_t)nb * 64;
+  const dim3 grid(nb), block(kThreads);
+  auto pass = [&](auto kern, double* coef, const double* cpart, double* part, int* kn) {
+    hipLaunchKernelGGL(kern, grid, block, 0, c->stream, V, ldv, k, kdev, coef, fused ? cpart : (const double*)nullptr,
+                       nb, w, n, part, kn);
   };
-  if (k <= 16) go(gs_update_dot_kernel<16>);
-  else if (k <= 24) go(gs_update_dot_kernel<24>);
-  else if (k <= 32) go(gs_update_dot_kernel<32>);
-  else if (k <= 40) go(gs_update_dot_kernel<40>);
-  else if (k <= 48) go(gs_update_dot_kernel<48>);
-  else go(gs_update_dot_kernel<64>);
-  hipLaunchKernelGGL(reduce_rows_kernel, dim3(k), dim3(kThreads), 0, c->stream, part, nb, coef2, kdev);
-  D3S_HIP(hipGetLastError());
-}
-
-void gs_update_norm(Ctx* c, const double* V, long ldv, int k, const int* kdev, const double* coef, double* w,
-                    long n, double* npart) {
-  if (k > 128) throw Error{D3S_EINVAL, "Gram-Schmidt: more than 128 vectors"};
-  hipLaunchKernelGGL(gs_update_norm_kernel, dim3(gs_blocks(n)), dim3(kThreads), 0, c->stream, V, ldv, k, kdev,
-                     coef, w, n, npart);
+  auto sums = [&](const double* part, double* coef) {
+    if (!fused) hipLaunchKernelGGL(reduce_rows_kernel, dim3(k), block, 0, c->stream, part, nb, coef, kdev);
+  };
+  pass(gs_pass_kernel<0>, nullptr, nullptr, p1, nullptr);
+  sums(p1, coef1);
+  pass(gs_pass_kernel<1>, coef1, p1, p2, nullptr);
+  sums(p2, coef2);
+  pass(gs_pass_kernel<2>, coef2, p2, npart, knext);
   D3S_HIP(hipGetLastError());
 }
 
@@ -873,22 +889,22 @@ void lanczos_tail(Ctx* c, const double* w, long n, const double* npart, const do
   D3S_HIP(hipGetLastError());
 }
 
-void copy_row_f64(Ctx* c, const double* V, long n, const int* kdev, double* dst) {
-  hipLaunchKernelGGL(copy_row_kernel, dim3(grid_for(n)), dim3(kThreads), 0, c->stream, V, n, kdev, dst);
+void copy_row_f64(Ctx* c, const double* V, long n, const int* knext, int* kcur, double* dst) {
+  hipLaunchKernelGGL(copy_row_kernel, dim3(grid_for(n)), dim3(kThreads), 0, c->stream, V, n, knext, kcur, dst);
   D3S_HIP(hipGetLastError());
 }
 
-void set_int_dev(Ctx* c, int* p, int v, bool add) {
-  hipLaunchKernelGGL(set_int_kernel, dim3(1), dim3(64), 0, c->stream, p, v, add ? 1 : 0);
+void set_int_dev(Ctx* c, int* p, int v) {
+  hipLaunchKernelGGL(set_int_kernel, dim3(1), dim3(64), 0, c->stream, p, v);
   D3S_HIP(hipGetLastError());
 }
 
 void maxpy_f64(Ctx* c, const double* V, long ldv, int k, const double* coef_dev, double sign, double* w,
-               long n, const int* kdev) {
+               long n, const int* kdev, bool accumulate) {
   if (k <= 0) return;
   if (k > 128) throw Error{D3S_EINVAL, "maxpy: more than 128 vectors"};
   hipLaunchKernelGGL(maxpy_kernel, dim3(grid_for(n)), dim3(kThreads), 0, c->stream, V, ldv, k, kdev, coef_dev,
-                     sign, w, n);
+                     sign, w, n, accumulate ? 1 : 0);
   D3S_HIP(hipGetLastError());
 }
 

@@ -717,32 +717,31 @@ struct Matvec {
 // One Lanczos run (with restarts) on the operator `mv`, starting from x
 // (normalised in place, overwritten by the Ritz vector).
 //
-// A step runs entirely on the device and reads its index k from device
-// memory: V_k is copied to a fixed input buffer, multiplied, orthogonalised
-// twice (classical Gram-Schmidt) against V_0..V_k, normalised into V_{k+1},
-// (alpha_k, beta_k) are stored and k is incremented.  Because nothing in it
-// depends on the host, the same step serves every k: with mv.use_graph it
-// is captured once into a hipGraph (after a first eager step has sized
-// every buffer) and replayed per step.  The host copies (alpha_k, beta_k)
-// to pinned memory, enqueues step k+1 before it reads step k and solves the
-// tridiagonal problem, so the device does not idle while the host tests
-// convergence; a step enqueued past convergence is discarded (the Ritz
-// vector uses V_0..V_k only).
+// A step multiplies V_k, orthogonalises the product twice (classical
+// Gram-Schmidt) against V_0..V_k, normalises it into V_{k+1} and stores
+// (alpha_k, beta_k) in pinned host memory.  With mv.use_graph it reads its
+// index k from device memory (V_k is copied to a fixed input buffer first), so
+// that nothing in it depends on the host: it is captured once into a hipGraph
+// (after a first eager step has sized every buffer) and replayed for every k.
+// Otherwise the host passes k, and the product reads V_k in place.  The host
+// enqueues step k+1 before it reads step k and solves the tridiagonal problem,
+// so the device does not idle while the host tests convergence; a step
+// enqueued past convergence is discarded (the Ritz vector uses V_0..V_k only).
 LanczosResult lanczos_core(Ctx* c, Matvec& mv, double* x, long n, double tol, int kmax, int max_mv,
                            bool use_f64) {
   const int kk = (int)std::min<long>(kmax, n);
   if (kk > 64) throw Error{D3S_EINVAL, "lanczos: at most 64 Krylov vectors"};
   double* V = (double*)ws_get(c, WS_LZ_V, sizeof(double) * (size_t)(kk + 1) * n);
   double* w = (double*)ws_get(c, WS_LZ_W, sizeof(double) * n);
-  double* xin = (double*)ws_get(c, WS_BLK_X, sizeof(double) * n);
+  const bool want_graph = mv.use_graph && !c->prof;
+  double* xin = want_graph ? (double*)ws_get(c, WS_BLK_X, sizeof(double) * n) : nullptr;
   double* cf = (double*)ws_get(c, WS_LZ_COEF, sizeof(double) * 1024);
-  int* kdev = (int*)ws_get(c, WS_LZ_K, 256);
+  int* kdev = (int*)ws_get(c, WS_LZ_K, 256);      // this step's index, then the next one's
   double* cf1 = cf;          // first Gram-Schmidt coefficients
   double* cf2 = cf + 128;    // second pass
   double* sc = cf + 256;     // scalars
   double* ydev = cf + 384;   // Ritz coefficients
-  double* ab = cf + 512;     // (alpha_k, beta_k) per step
-  double* hab = c->host_red + 256;   // pinned host copy of ab
+  volatile double* hab = c->host_red + 256;   // (alpha_k, beta_k) per step, written by the step itself
   LanczosResult res{0.0, 0, false, 0};
   if (!c->lz_ev[0]) {
     D3S_HIP(hipEventCreateWithFlags((hipEvent_t*)&c->lz_ev[0], hipEventDisableTiming));
@@ -760,21 +759,22 @@ LanczosResult lanczos_core(Ctx* c, Matvec& mv, double* x, long n, double tol, in
   scale_f64(c, x, n, 1.0 / std::sqrt(nrm2));
   copy_f64(c, x, V, n);
   double* npart = (double*)ws_get(c, WS_GS_NORM, sizeof(double) * kGsMaxBlocks);
-  auto body = [&]() {
-    copy_row_f64(c, V, n, kdev, xin);
-    mv.product(xin, w, use_f64);
-    // classical Gram-Schmidt twice against V_0..V_k, three passes over V:
-    // c1 = V^T w;  w -= V c1 with c2 = V^T w;  w -= V c2 with |w|^2
-    mdot_f64(c, V, n, kk, w, n, cf1, kdev);
-    gs_second_pass(c, V, n, kk, kdev, cf1, w, n, cf2);
-    gs_update_norm(c, V, n, kk, kdev, cf2, w, n, npart);
-    lanczos_tail(c, w, n, npart, cf1, cf2, 0, kdev, kk, V, ab);
-    set_int_dev(c, kdev, 1, true);
+  auto body = [&](int k) {
+    double* ab = c->host_red + 256;
+    if (want_graph) {
+      copy_row_f64(c, V, n, kdev + 1, kdev, xin);
+      mv.product(xin, w, use_f64);
+      gram_schmidt(c, V, n, kk, kdev, w, n, cf1, cf2, npart, kdev + 1);
+      lanczos_tail(c, w, n, npart, cf1, cf2, 0, kdev, kk, V, ab);
+    } else {
+      mv.product(V + (long)k * n, w, use_f64);
+      gram_schmidt(c, V, n, k + 1, nullptr, w, n, cf1, cf2, npart, nullptr);
+      lanczos_tail(c, w, n, npart, cf1, cf2, k, nullptr, kk, V, ab);
+    }
   };
   hipGraph_t graph = nullptr;
   hipGraphExec_t gexec = nullptr;
   hipStream_t cap = nullptr;
-  const bool want_graph = mv.use_graph && !c->prof;
   auto cleanup = [&]() {
     if (gexec) (void)hipGraphExecDestroy(gexec);
     if (graph) (void)hipGraphDestroy(graph);
@@ -787,7 +787,7 @@ LanczosResult lanczos_core(Ctx* c, Matvec& mv, double* x, long n, double tol, in
     if (gexec) {
       D3S_HIP(hipGraphLaunch(gexec, c->stream));
     } else {
-      body();
+      body(k);
       if (want_graph) {
         // every buffer is sized now: capture the step on a private stream
         hipStream_t keep = c->stream;
@@ -795,7 +795,7 @@ LanczosResult lanczos_core(Ctx* c, Matvec& mv, double* x, long n, double tol, in
         c->stream = cap;
         D3S_HIP(hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal));
         try {
-          body();
+          body(k);
         } catch (...) {
           hipGraph_t g = nullptr;
           (void)hipStreamEndCapture(cap, &g);
@@ -808,7 +808,6 @@ LanczosResult lanczos_core(Ctx* c, Matvec& mv, double* x, long n, double tol, in
         D3S_HIP(hipGraphInstantiate(&gexec, graph, nullptr, nullptr, 0));
       }
     }
-    D3S_HIP(hipMemcpyAsync(hab + 2 * k, ab + 2 * k, 2 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
     D3S_HIP(hipEventRecord((hipEvent_t)c->lz_ev[k & 1], c->stream));
     res.matvecs++;
   };
@@ -819,7 +818,7 @@ LanczosResult lanczos_core(Ctx* c, Matvec& mv, double* x, long n, double tol, in
       betas.clear();
       bool stop = false;
       std::vector<double> y;
-      set_int_dev(c, kdev, 0, false);
+      if (want_graph) set_int_dev(c, kdev + 1, 0);
       enqueue_step(0);
       int enq = 1;
       for (int k = 0; k < kk; ++k) {
@@ -856,13 +855,14 @@ LanczosResult lanczos_core(Ctx* c, Matvec& mv, double* x, long n, double tol, in
         betas.push_back(b);
       }
       const int m = (int)y.size();
-      // Ritz vector x = sum_j y_j V_j (stream-ordered after any step still in flight)
-      write_many(c, ydev, y.data(), m);
-      fill_f64(c, x, n, 0.0);
-      maxpy_f64(c, V, n, m, ydev, 1.0, x, n);
+      // Ritz vector x = sum_j y_j V_j (stream-ordered after any step still in
+      // flight), its coefficients through pinned memory that is next written
+      // by a later run, after this one's final synchronisation or its events
+      for (int j = 0; j < m; ++j) c->host_red[128 + j] = y[j];
+      D3S_HIP(hipMemcpyAsync(ydev, c->host_red + 128, sizeof(double) * m, hipMemcpyHostToDevice, c->stream));
+      maxpy_f64(c, V, n, m, ydev, 1.0, x, n, nullptr, false);
       dot_f64(c, x, x, n, sc);
-      const double xn = read_scalar(c, sc);
-      scale_f64(c, x, n, 1.0 / std::sqrt(xn));
+      scale_by_dev_f64(c, x, n, sc, true);
       if (stop) break;
       res.restarts++;
       copy_f64(c, x, V, n);
