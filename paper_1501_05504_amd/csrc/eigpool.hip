@@ -160,7 +160,7 @@ void run_share(const std::vector<EigCall>& calls, const std::vector<int>& mine, 
 }  // namespace
 
 void eig_calls_parallel(Ctx* c, const std::vector<EigCall>& calls, const std::vector<int>& worker, int workers,
-                        double* G, double* V) {
+                        double* G, double* V, const std::function<void()>& first) {
   // share 0 runs here on the context's stream, shares 1.. on pool threads
   EigPool* P = pool_of(c, workers - 1);
   if (!c->solver) {
@@ -209,6 +209,7 @@ void eig_calls_parallel(Ctx* c, const std::vector<EigCall>& calls, const std::ve
   d3s_status code = D3S_OK;
   std::string msg;
   try {
+    first();
     run_share(calls, mine0, c->stream, own, nullptr, scratch, eo, io, G, V);
   } catch (const Error& e) {
     code = e.code;

@@ -1164,219 +1164,6 @@ void transpose_tiles(Ctx* c, int esz, const void* in, void* out, const TrTile* t
   D3S_HIP(hipGetLastError());
 }
 
-// ---------------------------------------------------------------- small symmetric eigensolver
-// Batched FP64 symmetric eigensolver for n <= kEigSmallMax, one workgroup
-// per matrix with the whole matrix in LDS (rows of odd stride n+1, so column
-// walks do not collide in the banks): Householder reduction to tridiagonal
-// form with the orthogonal transformation accumulated in place, then the
-// implicit QL iteration with shifts on the tridiagonal matrix (the classical
-// tred2 / tql2 pair of Wilkinson and Reinsch's Handbook).  The scalar
-// recurrence of each QL sweep runs on one thread, which stores the sweep's
-// Givens rotations; all threads then apply them to the rows of the
-// eigenvector matrix.  Nothing is launched per column, which is what makes
-// the library solver slow on batches of small Gram matrices.
-__device__ __forceinline__ double eig_allsum(double v, double* red) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-  __syncthreads();                       // red may still be read from the previous call
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  double r = 0.0;
-  for (int w = 0; w < (int)(blockDim.x >> 6); ++w) r += red[w];
-  return r;                              // the same sum, in the same order, on every thread
-}
-
-template <int NMAX>
-__global__ __launch_bounds__(kThreads)
-void eig_small_kernel(double* __restrict__ A, double* __restrict__ evals, int n, int* __restrict__ info) {
-  constexpr int LD = NMAX + 1;
-  __shared__ double a[NMAX * LD];
-  __shared__ double d[NMAX], e[NMAX], cs[2 * NMAX], red[8];
-  __shared__ int ctl[4], perm[NMAX];
-  const int tid = threadIdx.x, nt = blockDim.x;
-  const int ld = n + 1;
-  double* Ab = A + (long)blockIdx.x * n * n;
-  // symmetric: the column-major input read row by row is the same matrix
-  for (int idx = tid; idx < n * n; idx += nt) a[(idx / n) * ld + idx % n] = Ab[idx];
-  __syncthreads();
-  // ---- Householder reduction (row i annihilated left of the subdiagonal)
-  for (int i = n - 1; i > 0; --i) {
-    const int l = i - 1;
-    double h = 0.0;
-    double* ai = a + i * ld;
-    if (l > 0) {
-      double part = 0.0;
-      for (int k = tid; k <= l; k += nt) part += fabs(ai[k]);
-      const double scale = eig_allsum(part, red);
-      if (scale == 0.0) {
-        if (tid == 0) e[i] = ai[l];
-        __syncthreads();
-      } else {
-        part = 0.0;
-        for (int k = tid; k <= l; k += nt) {
-          const double v = ai[k] / scale;
-          ai[k] = v;
-          part += v * v;
-        }
-        h = eig_allsum(part, red);
-        const double f = ai[l];
-        const double g = (f >= 0.0) ? -sqrt(h) : sqrt(h);
-        h -= f * g;
-        __syncthreads();                 // every thread has read ai[l]
-        if (tid == 0) {
-          e[i] = scale * g;
-          ai[l] = f - g;                 // u = row i, H = h
-        }
-        __syncthreads();
-        // p = A u / H into e[0..l], u / H into column i
-        part = 0.0;
-        for (int j = tid; j <= l; j += nt) {
-          a[j * ld + i] = ai[j] / h;
-          double gg = 0.0;
-          for (int k = 0; k <= j; ++k) gg += a[j * ld + k] * ai[k];
-          for (int k = j + 1; k <= l; ++k) gg += a[k * ld + j] * ai[k];
-          e[j] = gg / h;
-          part += e[j] * ai[j];
-        }
-        const double hh = eig_allsum(part, red) / (h + h);
-        for (int j = tid; j <= l; j += nt) e[j] -= hh * ai[j];      // q = p - K u
-        __syncthreads();
-        // A -= u q^T + q u^T on the lower triangle of the leading block
-        for (int j = tid; j <= l; j += nt) {
-          const double fj = ai[j], gj = e[j];
-          for (int k = 0; k <= j; ++k) a[j * ld + k] -= fj * e[k] + gj * ai[k];
-        }
-        __syncthreads();
-      }
-    } else {
-      if (tid == 0) e[i] = ai[l];
-      __syncthreads();
-    }
-    if (tid == 0) d[i] = h;
-    __syncthreads();
-  }
-  if (tid == 0) {
-    d[0] = 0.0;
-    e[0] = 0.0;
-  }
-  __syncthreads();
-  // ---- accumulate the transformation: a becomes the orthogonal matrix
-  for (int i = 0; i < n; ++i) {
-    const int l = i - 1;
-    const bool nz = (d[i] != 0.0);
-    __syncthreads();                     // d[i] is rewritten below
-    if (nz) {
-      for (int j = tid; j <= l; j += nt) {
-        double g = 0.0;
-        for (int k = 0; k <= l; ++k) g += a[i * ld + k] * a[k * ld + j];
-        for (int k = 0; k <= l; ++k) a[k * ld + j] -= g * a[k * ld + i];
-      }
-      __syncthreads();
-    }
-    if (tid == 0) {
-      d[i] = a[i * ld + i];
-      a[i * ld + i] = 1.0;
-    }
-    for (int j = tid; j <= l; j += nt) {
-      a[j * ld + i] = 0.0;
-      a[i * ld + j] = 0.0;
-    }
-    __syncthreads();
-  }
-  // ---- implicit QL on the tridiagonal (d, e), rotations applied to the rows of a
-  if (tid == 0) {
-    for (int i = 1; i < n; ++i) e[i - 1] = e[i];
-    e[n - 1] = 0.0;
-    ctl[2] = 0;
-  }
-  __syncthreads();
-  for (int l = 0; l < n; ++l) {
-    int iter = 0;
-    while (true) {
-      if (tid == 0) {
-        int m = l;
-        for (; m < n - 1; ++m) {
-          const double dd = fabs(d[m]) + fabs(d[m + 1]);
-          if (fabs(e[m]) + dd == dd) break;
-        }
-        int ilo = m - 1;                 // no rotation
-        if (m != l) {
-          if (iter++ >= 60) {
-            ctl[2] = 1;                  // no convergence: stop this eigenvalue
-            m = l;
-          } else {
-            double g = (d[l + 1] - d[l]) / (2.0 * e[l]);
-            double r = hypot(g, 1.0);
-            g = d[m] - d[l] + e[l] / (g + copysign(r, g));
-            double sn = 1.0, cn = 1.0, p = 0.0;
-            int i = m - 1;
-            for (; i >= l; --i) {
-              const double f = sn * e[i], b = cn * e[i];
-              r = hypot(f, g);
-              e[i + 1] = r;
-              if (r == 0.0) {
-                d[i + 1] -= p;
-                e[m] = 0.0;
-                break;
-              }
-              sn = f / r;
-              cn = g / r;
-              g = d[i + 1] - p;
-              r = (d[i] - g) * sn + 2.0 * cn * b;
-              p = sn * r;
-              d[i + 1] = g + p;
-              g = cn * r - b;
-              cs[2 * i] = cn;
-              cs[2 * i + 1] = sn;
-            }
-            ilo = i;                     // rotations ilo+1 .. m-1 were formed
-            if (!(r == 0.0 && i >= l)) {
-              d[l] -= p;
-              e[l] = g;
-              e[m] = 0.0;
-            }
-          }
-        }
-        ctl[0] = m;
-        ctl[1] = ilo;
-      }
-      __syncthreads();
-      const int m = ctl[0], ilo = ctl[1];
-      __syncthreads();                   // ctl is rewritten in the next pass
-      if (m == l) break;
-      for (int k = tid; k < n; k += nt) {
-        double* zk = a + k * ld;
-        for (int i = m - 1; i > ilo; --i) {
-          const double cn = cs[2 * i], sn = cs[2 * i + 1];
-          const double f = zk[i + 1];
-          zk[i + 1] = sn * zk[i] + cn * f;
-          zk[i] = cn * zk[i] - sn * f;
-        }
-      }
-      __syncthreads();
-    }
-  }
-  // ---- ascending order; eigenvector r = column perm[r] of a
-  if (tid == 0) {
-    for (int i = 0; i < n; ++i) perm[i] = i;
-    for (int i = 0; i < n; ++i) {
-      int best = i;
-      for (int j = i + 1; j < n; ++j)
-        if (d[perm[j]] < d[perm[best]]) best = j;
-      const int t = perm[i];
-      perm[i] = perm[best];
-      perm[best] = t;
-    }
-    info[blockIdx.x] = ctl[2];
-  }
-  __syncthreads();
-  double* wb = evals + (long)blockIdx.x * n;
-  for (int r = tid; r < n; r += nt) wb[r] = d[perm[r]];
-  for (int idx = tid; idx < n * n; idx += nt) {
-    const int r = idx / n, k = idx % n;
-    Ab[idx] = a[k * ld + perm[r]];
-  }
-}
-
 void relayout_tiles(Ctx* c, int in_kind, int out_kind, const void* in, void* out, const RlTile* tiles,
                     int ntiles) {
   if (ntiles <= 0) return;
@@ -1399,36 +1186,6 @@ void relayout_tiles(Ctx* c, int in_kind, int out_kind, const void* in, void* out
   else
     throw Error{D3S_EINVAL, "relayout: unsupported element types"};
   D3S_HIP(hipGetLastError());
-}
-
-// Batched symmetric eigensolver (eigenvalues ascending, eigenvectors as the
-// columns of the column-major matrices): the LDS solver above for
-// n <= kEigSmallMax when chosen (d3s_set_eigensolver kind 3), rocSOLVER
-// otherwise.  Measured on MI355X the LDS solver takes about 0.11 / 0.8 /
-// 2.6 / 6.1 ms for n = 8 / 32 / 64 / 96 whatever the batch (up to 256
-// matrices side by side): the Householder and accumulation phases have
-// about n threads each walking O(n) dependent LDS operations, so it beats
-// rocSOLVER only on batches of small matrices.
-bool eig_small_used(const Ctx* c, int n) { return c->eig_kind == 3 && n >= 1 && n <= kEigSmallMax; }
-
-void eig_batched_f64(Ctx* c, int n, int batch, double* A, double* evals) {
-  if (batch <= 0) return;
-  if (!eig_small_used(c, n)) {
-    syevd_batched_f64(c, n, batch, A, evals);
-    return;
-  }
-  int* info = (int*)ws_get(c, WS_INFO, sizeof(int) * (size_t)batch);
-  const dim3 g((unsigned)batch), b(kThreads);
-  if (n <= 32) hipLaunchKernelGGL(eig_small_kernel<32>, g, b, 0, c->stream, A, evals, n, info);
-  else if (n <= 64) hipLaunchKernelGGL(eig_small_kernel<64>, g, b, 0, c->stream, A, evals, n, info);
-  else if (n <= 96) hipLaunchKernelGGL(eig_small_kernel<96>, g, b, 0, c->stream, A, evals, n, info);
-  else hipLaunchKernelGGL(eig_small_kernel<kEigSmallMax>, g, b, 0, c->stream, A, evals, n, info);
-  D3S_HIP(hipGetLastError());
-  std::vector<int> h(batch);
-  D3S_HIP(hipMemcpyAsync(h.data(), info, sizeof(int) * batch, hipMemcpyDeviceToHost, c->stream));
-  D3S_HIP(hipStreamSynchronize(c->stream));
-  for (int q = 0; q < batch; ++q)
-    if (h[q] != 0) throw Error{D3S_EDEVICE, "small eigensolver: the QL iteration did not converge"};
 }
 
 void copy2d_f64(Ctx* c, const double* src, long lds, double* dst, long ldd, long rows, long cols) {

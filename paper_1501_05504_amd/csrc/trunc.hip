@@ -36,6 +36,7 @@
 #include <chrono>
 #include <cfloat>
 #include <cmath>
+#include <cstring>
 #include <map>
 
 #include "d3s_internal.h"
@@ -137,13 +138,13 @@ void multi_gemm(Ctx* c, const std::vector<MTask>& ts, bool a_kc, bool b_kc, cons
 // dsyevd_strided_batched): from n = 96 on a call costs about 24 us per
 // matrix column whatever the batch size (launch-bound) plus ~1.6e-12 n^3 s
 // per matrix, while below n = 96 its batched small-size path grows steeply
-// with the batch (n = 64, 40 matrices: 18 ms against 2 ms at n = 96).  With
-// the LDS solver chosen, matrices up to 128 may go to it instead (one
-// workgroup per matrix, nothing launched per column, about 5e-5 + 6.5e-7 n^2
-// s per batch of up to 256).  Sizes are padded (to a multiple of 8 for the
-// LDS solver, else to at least 96 and a multiple of 16; a lone matrix is not
-// padded), sorted, and grouped contiguously with the least modelled cost
-// (dynamic programming).
+// with the batch (n = 64, 40 matrices: 18 ms against 2 ms at n = 96).  The
+// library's own solver takes the small ones (one workgroup per matrix, one
+// launch; a batch of up to 256 takes 0.13 ms at n = 32, 0.25 ms at n = 64 and
+// 0.49 ms at n = 96).  Sizes are padded
+// (to a multiple of 8 for the own solver, else to at least 96 and a multiple
+// of 16; a lone matrix is not padded), sorted, and grouped contiguously with
+// the least modelled cost (dynamic programming).
 EigPlan plan_eig(Ctx* c, const std::vector<int>& n) {
   EigPlan ep;
   const int Q = (int)n.size();
@@ -157,7 +158,7 @@ EigPlan plan_eig(Ctx* c, const std::vector<int>& n) {
   std::stable_sort(ord.begin(), ord.end(), [&](int a, int b) { return n[a] < n[b]; });
   auto small = [&](int m) { return eig_small_used(c, (m + 7) / 8 * 8); };
   auto pad = [&](int m, int cnt) {
-    if (small(m)) return (m + 7) / 8 * 8;
+    if (small(m)) return cnt == 1 ? m : (m + 7) / 8 * 8;
     return cnt == 1 ? m : std::max(96, (m + 15) / 16 * 16);
   };
   // With K concurrent shares (below) the launch chains of separate calls
@@ -169,7 +170,7 @@ EigPlan plan_eig(Ctx* c, const std::vector<int>& n) {
   auto cost = [&](int i, int j) {
     const int cnt = j - i + 1;
     const double np = pad(n[ord[j]], cnt);
-    if (small(n[ord[j]])) return (5e-5 + 6.5e-7 * np * np) * ((cnt + 255) / 256);
+    if (small(n[ord[j]])) return (3e-5 + (np <= 64 ? 3.4e-6 : 4.8e-6) * np) * ((cnt + 255) / 256);
     return col * np + 1.6e-12 * (double)cnt * np * np * np;
   };
   const int G = (int)ord.size();
@@ -203,7 +204,7 @@ EigPlan plan_eig(Ctx* c, const std::vector<int>& n) {
       ep.vtot += np;
       ep.members.back().push_back(q);
     }
-    ep.calls.push_back(EigCall{np, cnt, ep.bucket_goff.back(), ep.bucket_voff.back()});
+    if (!eig_small_used(c, np)) ep.calls.push_back(EigCall{np, cnt, ep.bucket_goff.back(), ep.bucket_voff.back()});
   }
   // Concurrent solves (divide and conquer only): each call's cost model as
   // above; the calls are dealt to the workers largest first, each to the
@@ -211,8 +212,7 @@ EigPlan plan_eig(Ctx* c, const std::vector<int>& n) {
   // two calls on consecutive matrices) while that lowers the largest load.
   const int K = c->eig_workers;
   bool all_dc = c->eig_kind != 2;
-  for (int b : ep.bucket_n)
-    all_dc = all_dc && !eig_small_used(c, b) && !(c->eig_kind == 0 && b <= c->eig_jacobi_max);
+  for (int b : ep.bucket_n) all_dc = all_dc && (eig_small_used(c, b) || !(c->eig_kind == 0 && b <= c->eig_jacobi_max));
   if (K >= 2 && all_dc && !ep.calls.empty()) {
     auto cc = [](const EigCall& e) { return 2.4e-5 * e.n + 1.6e-12 * (double)e.batch * e.n * e.n * (double)e.n; };
     auto assign = [&](std::vector<EigCall>& calls, std::vector<int>& who) {
@@ -294,11 +294,37 @@ void eig_run(Ctx* c, const EigPlan& ep, const std::vector<int>& n, double* G, do
   D3S_HIP(hipGetLastError());
   D3S_HIP(hipStreamSynchronize(c->stream));
   const auto t0 = std::chrono::steady_clock::now();
+  // the own solver's buckets are a launch each on the context's stream, issued
+  // once the concurrent shares have been started; their flags are read last
+  std::vector<size_t> own;
+  int nown = 0;
+  for (size_t b = 0; b < ep.bucket_n.size(); ++b)
+    if (eig_small_used(c, ep.bucket_n[b])) {
+      own.push_back(b);
+      nown += (int)ep.members[b].size();
+    }
+  int* info = nown ? (int*)ws_get(c, WS_EIG_INFO, sizeof(int) * (size_t)nown) : nullptr;
+  auto launch_own = [&]() {
+    int at = 0;
+    for (size_t b : own) {
+      eig_small_launch(c, ep.bucket_n[b], (int)ep.members[b].size(), G + ep.bucket_goff[b], V + ep.bucket_voff[b],
+                       info + at);
+      at += (int)ep.members[b].size();
+    }
+  };
   if (ep.workers >= 2) {
-    eig_calls_parallel(c, ep.calls, ep.worker, ep.workers, G, V);
+    eig_calls_parallel(c, ep.calls, ep.worker, ep.workers, G, V, launch_own);
   } else {
+    launch_own();
     for (size_t b = 0; b < ep.bucket_n.size(); ++b)
-      eig_batched_f64(c, ep.bucket_n[b], (int)ep.members[b].size(), G + ep.bucket_goff[b], V + ep.bucket_voff[b]);
+      if (!eig_small_used(c, ep.bucket_n[b]))
+        eig_batched_f64(c, ep.bucket_n[b], (int)ep.members[b].size(), G + ep.bucket_goff[b], V + ep.bucket_voff[b]);
+  }
+  if (nown) {
+    std::vector<int> h(nown);
+    D3S_HIP(hipMemcpyAsync(h.data(), info, sizeof(int) * nown, hipMemcpyDeviceToHost, c->stream));
+    D3S_HIP(hipStreamSynchronize(c->stream));
+    eig_small_check(h.data(), nown);
   }
   // every solve path ends with a readback of its convergence flags
   c->stat_eig_s += std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
@@ -340,8 +366,12 @@ void trunc_solve(Ctx* c, const TruncMats& tm, int kmax, double eps, TruncSel& ou
       if (solve[q]) nsolve[q] = st[q].n;
     const EigPlan ep = plan_eig(c, nsolve);
     double* G = (double*)ws_get(c, pass == 1 ? WS_GPACK : WS_TR_G, sizeof(double) * (size_t)std::max(ep.gtot, 1L));
-    double* V = (double*)ws_get(c, pass == 1 ? WS_GVAL : WS_TR_V, sizeof(double) * (size_t)std::max(ep.vtot, 1L));
-    zero_bytes(c, G, sizeof(double) * (size_t)ep.gtot);
+    double* V = (double*)ws_get(c, pass == 1 ? WS_GVAL : WS_TR_V, sizeof(double) * (size_t)(ep.vtot + 1));
+    // one small matrix (a dense truncation): unpadded, so its Gram product
+    // covers it, scaled inside the solver, and its eigenvalues and flag
+    // (stored behind them) come back together
+    const bool lone = ep.bucket_n.size() == 1 && ep.members[0].size() == 1 && eig_small_used(c, ep.bucket_n[0]);
+    if (!lone) zero_bytes(c, G, sizeof(double) * (size_t)ep.gtot);
     {
       std::vector<MTask> ts;
       for (int q = 0; q < Q; ++q)
@@ -355,10 +385,24 @@ void trunc_solve(Ctx* c, const TruncMats& tm, int kmax, double eps, TruncSel& ou
       multi_gemm(c, ts, true, true, zb, zb, G, 1.0, 0.0);
     }
     std::vector<double> gscale;
-    eig_run(c, ep, nsolve, G, V, gscale);
-    std::vector<double> ev(std::max(ep.vtot, 1L));
-    D3S_HIP(hipMemcpyAsync(ev.data(), V, sizeof(double) * (size_t)ep.vtot, hipMemcpyDeviceToHost, c->stream));
+    std::vector<double> ev(ep.vtot + 1);
+    const auto te = std::chrono::steady_clock::now();
+    if (lone) {
+      gscale.assign(Q, 1.0);
+      eig_small_launch(c, ep.bucket_n[0], 1, G, V, reinterpret_cast<int*>(V + ep.vtot));
+    } else {
+      eig_run(c, ep, nsolve, G, V, gscale);
+    }
+    D3S_HIP(hipMemcpyAsync(ev.data(), V, sizeof(double) * (size_t)(ep.vtot + (lone ? 1 : 0)), hipMemcpyDeviceToHost,
+                           c->stream));
     D3S_HIP(hipStreamSynchronize(c->stream));
+    if (lone) {
+      c->stat_eig_s += std::chrono::duration<double>(std::chrono::steady_clock::now() - te).count();
+      int flag;
+      std::memcpy(&flag, &ev[ep.vtot], sizeof(int));
+      if (flag == 2) throw Error{D3S_ENUMERIC, "truncate: the expanded tensor is not finite"};
+      eig_small_check(&flag, 1);
+    }
     // ---- accepted values; the vectors of this pass
     // pass >= 2: T' = Y_real^T T into this pass's own buffer (its accepted
     // rows are the results and must survive later passes)

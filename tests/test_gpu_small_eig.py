@@ -1,0 +1,77 @@
+"""The library's own small eigensolver (csrc/eigsmall.hip) against the
+eigenpair equations and LAPACK's eigenvalues, at the sizes where its leaves,
+levels and workgroups change (16, 32, 64 and the 96 it ends at), on spectra that
+deflate in every way: none, graded, clustered, repeated, zero, block diagonal.
+
+Tolerance: 10 n u |A| for the residual and the eigenvalues, 10 n u for the
+orthogonality, u = 2.2e-16; the bound p(n) u of a backward stable reduction
+with p linear."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+abi = pytest.importorskip("paper_1501_05504_amd.abi")
+
+DEV = torch.device("cuda:0")
+U = 2.2e-16
+SIZES = [1, 2, 3, 7, 8, 15, 16, 17, 31, 32, 33, 47, 48, 63, 64, 65, 95, 96]
+
+
+def matrices(n):
+    rng = np.random.default_rng(n)
+    q, _ = np.linalg.qr(rng.standard_normal((n, n)))
+    r = rng.standard_normal((n, n))
+    lam = {
+        "uniform": np.linspace(-1, 1, n),
+        "graded": np.logspace(0, -30, n),
+        "clustered": 1 + 1e-13 * np.arange(n),
+        "two values": np.where(np.arange(n) % 3 == 0, 2.0, 1.0),
+        "low rank": np.where(np.arange(n) < (n + 3) // 4, np.arange(n) + 1.0, 0.0),
+    }
+    ms = {k: (q * v) @ q.T for k, v in lam.items()}
+    ms["random"] = r
+    ms["large"] = 1e200 * r
+    ms["small"] = 1e-200 * r
+    ms["zero"] = np.zeros((n, n))
+    ms["diagonal"] = np.diag(np.sort(rng.standard_normal(n))[::-1])
+    ms["blocks"] = np.kron(np.eye((n + 3) // 4), r[:4, :4] if n >= 4 else np.ones((4, 4)))[:n, :n]
+    ms["second difference"] = 2 * np.eye(n) - np.eye(n, k=1) - np.eye(n, k=-1)
+    ms["wilkinson"] = np.diag(np.abs(np.arange(n) - (n - 1) / 2)) + np.eye(n, k=1) + np.eye(n, k=-1)
+    return {k: (m + m.T) / 2 for k, m in ms.items()}
+
+
+@pytest.mark.parametrize("n", SIZES)
+@pytest.mark.parametrize("kind", [0, 3])
+def test_eigenpairs(n, kind):
+    ms = matrices(n)
+    G = np.stack(list(ms.values()))
+    A = torch.tensor(G, device=DEV)
+    W = torch.empty(len(G), n, dtype=torch.float64, device=DEV)
+    c = abi.Context(0)
+    c.set_eigensolver(kind)
+    c.eig_batched(A, W)
+    c.close()
+    V, w = A.cpu().numpy(), W.cpu().numpy()          # rows of V[b]: eigenvectors
+    for b, name in enumerate(ms):
+        s = np.abs(G[b]).max() or 1.0
+        g, wb = G[b] / s, w[b] / s
+        norm = np.linalg.norm(g, 2)
+        assert np.all(np.diff(wb) >= 0), name
+        assert np.abs(g @ V[b].T - V[b].T * wb).max() <= 10 * n * U * norm, name
+        assert np.abs(V[b] @ V[b].T - np.eye(n)).max() <= 10 * n * U, name
+        assert np.abs(np.linalg.eigvalsh(g) - wb).max() <= 10 * n * U * norm, name
+
+
+@pytest.mark.parametrize("n", [5, 40, 96])
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+def test_a_matrix_that_is_not_finite_is_refused(n, bad):
+    A = torch.eye(n, dtype=torch.float64, device=DEV).repeat(3, 1, 1)
+    A[1, n - 1, 0] = bad
+    A[1, 0, n - 1] = bad
+    W = torch.empty(3, n, dtype=torch.float64, device=DEV)
+    c = abi.Context(0)
+    with pytest.raises(abi.D3SError):
+        c.eig_batched(A, W)
+    c.close()
