@@ -298,7 +298,8 @@ class Context:
 
     def set_eigensolver(self, kind, jacobi_max_n=0):
         """0 auto (Jacobi up to jacobi_max_n, else as 3), 1 rocSOLVER divide and
-        conquer, 2 Jacobi, 3 the library's own solver up to n = 96 and 1 above."""
+        conquer, 2 Jacobi, 3 the library's own solver (n <= 96, a single matrix
+        n <= 1024), else 1."""
         self._check(_set_eig(self.h, int(kind), int(jacobi_max_n)))
 
     def set_eig_workers(self, workers):

@@ -41,7 +41,7 @@ enum WsSlot {
   WS_EIGTMP, WS_UKT, WS_X, WS_MT, WS_CAST_L, WS_CAST_R, WS_CAST_X, WS_CAST_Y,
   WS_CAST_W, WS_REF, WS_PSI, WS_INFO, WS_NBR, WS_MISC, WS_SPLITK, WS_DESC, WS_BLK_X, WS_XPACK, WS_GPACK, WS_GVAL, WS_TUNE, WS_PK, WS_LZ_K, WS_GS_NORM, WS_JD_V, WS_JD_W, WS_JD_Z, WS_JD_COEF, WS_G2_PART, WS_W2, WS_RMET, WS_RZ, WS_RT, WS_RGRAM, WS_H2, WS_PSIT, WS_LP_L, WS_LP_R, WS_LP_X, WS_LP_Y,
   WS_TR_G, WS_TR_V, WS_TR_W0, WS_TR_W1, WS_TR_T2, WS_TR_T3, WS_TR_T4, WS_TR_P, WS_TR_TAB, WS_TR_AUX, WS_TR_XT,
-  WS_EIG_PAR, WS_EIG_INFO,
+  WS_EIG_PAR, WS_EIG_INFO, WS_EIG_MID,
   WS_NSLOTS
 };
 
@@ -560,6 +560,14 @@ constexpr int kEigSmallMax = 96;
 bool eig_small_used(const Ctx* c, int n);
 void eig_small_launch(Ctx* c, int n, int batch, double* A, double* evals, int* info);
 void eig_small_check(const int* info, int batch);
+// One matrix of kEigSmallMax < n <= kEigMidMax over the whole device
+// (eigmid.hip); only launches, as above; false: no memory for its scratch,
+// nothing was launched.  Up to the size whose row fits a wave's registers; at
+// n = 128 / 512 / 1024 it takes 0.6 / 2.4 / 7.0 ms, syevd 2.2 / 11.3 / 22.5.
+// Several matrices stay with syevd, whose launches a batch shares.
+constexpr int kEigMidMax = 1024;
+bool eig_mid_used(const Ctx* c, int n, int batch);
+bool eig_mid_launch(Ctx* c, int n, double* A, double* evals, int* info);
 void eig_batched_f64(Ctx* c, int n, int batch, double* A, double* evals);
 
 // lowest eigenpair of a symmetric tridiagonal matrix (bisection + inverse iteration)

@@ -1,7 +1,7 @@
-"""The library's own small eigensolver (csrc/eigsmall.hip) against the
-eigenpair equations and LAPACK's eigenvalues, at the sizes where its leaves,
-levels and workgroups change (16, 32, 64 and the 96 it ends at), on spectra that
-deflate in every way: none, graded, clustered, repeated, zero, block diagonal.
+"""The library's own eigensolvers (csrc/eigsmall.hip, csrc/eigmid.hip) against
+the eigenpair equations and LAPACK's eigenvalues, at the sizes where their leaves,
+levels and workgroups change (16, 32, 64, 96; powers of two and multiples of 256
+to the 1024 where they end), on spectra that deflate in every way: none, graded, clustered, repeated, zero, block diagonal.
 
 Tolerance: 10 n u |A| for the residual and the eigenvalues, 10 n u for the
 orthogonality, u = 2.2e-16; the bound p(n) u of a backward stable reduction
@@ -42,6 +42,17 @@ def matrices(n):
     return {k: (m + m.T) / 2 for k, m in ms.items()}
 
 
+def check(n, ms, G, V, w):                            # rows of V[b]: eigenvectors
+    for b, name in enumerate(ms):
+        s = np.abs(G[b]).max() or 1.0
+        g, wb = G[b] / s, w[b] / s
+        norm = np.linalg.norm(g, 2)
+        assert np.all(np.diff(wb) >= 0), name
+        assert np.abs(g @ V[b].T - V[b].T * wb).max() <= 10 * n * U * norm, name
+        assert np.abs(V[b] @ V[b].T - np.eye(n)).max() <= 10 * n * U, name
+        assert np.abs(np.linalg.eigvalsh(g) - wb).max() <= 10 * n * U * norm, name
+
+
 @pytest.mark.parametrize("n", SIZES)
 @pytest.mark.parametrize("kind", [0, 3])
 def test_eigenpairs(n, kind):
@@ -53,24 +64,29 @@ def test_eigenpairs(n, kind):
     c.set_eigensolver(kind)
     c.eig_batched(A, W)
     c.close()
-    V, w = A.cpu().numpy(), W.cpu().numpy()          # rows of V[b]: eigenvectors
-    for b, name in enumerate(ms):
-        s = np.abs(G[b]).max() or 1.0
-        g, wb = G[b] / s, w[b] / s
-        norm = np.linalg.norm(g, 2)
-        assert np.all(np.diff(wb) >= 0), name
-        assert np.abs(g @ V[b].T - V[b].T * wb).max() <= 10 * n * U * norm, name
-        assert np.abs(V[b] @ V[b].T - np.eye(n)).max() <= 10 * n * U, name
-        assert np.abs(np.linalg.eigvalsh(g) - wb).max() <= 10 * n * U * norm, name
+    check(n, ms, G, A.cpu().numpy(), W.cpu().numpy())
 
 
-@pytest.mark.parametrize("n", [5, 40, 96])
+@pytest.mark.parametrize("n", [97, 127, 128, 129, 192, 193, 255, 256, 257, 511, 512, 513, 769, 1023, 1024])
+def test_eigenpairs_of_one_matrix(n):
+    ms = matrices(n)
+    G = np.stack(list(ms.values()))
+    A = torch.tensor(G, device=DEV)
+    W = torch.empty(len(G), n, dtype=torch.float64, device=DEV)
+    c = abi.Context(0)
+    for b in range(len(G)):
+        c.eig_batched(A[b:b + 1], W[b:b + 1])
+    c.close()
+    check(n, ms, G, A.cpu().numpy(), W.cpu().numpy())
+
+
+@pytest.mark.parametrize("n, batch", [(5, 3), (40, 3), (96, 3), (97, 1), (300, 1)])
 @pytest.mark.parametrize("bad", [np.nan, np.inf])
-def test_a_matrix_that_is_not_finite_is_refused(n, bad):
-    A = torch.eye(n, dtype=torch.float64, device=DEV).repeat(3, 1, 1)
-    A[1, n - 1, 0] = bad
-    A[1, 0, n - 1] = bad
-    W = torch.empty(3, n, dtype=torch.float64, device=DEV)
+def test_a_matrix_that_is_not_finite_is_refused(n, batch, bad):
+    A = torch.eye(n, dtype=torch.float64, device=DEV).repeat(batch, 1, 1)
+    A[-1, n - 1, 0] = bad
+    A[-1, 0, n - 1] = bad
+    W = torch.empty(batch, n, dtype=torch.float64, device=DEV)
     c = abi.Context(0)
     with pytest.raises(abi.D3SError):
         c.eig_batched(A, W)
