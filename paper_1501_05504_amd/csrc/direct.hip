@@ -509,8 +509,10 @@ bool direct_dispatch(Ctx* c, const GemmArgs& g) {
   //  - fewer 32x32 tiles than compute units: eight waves a tile while each
   //    gets two K steps or more, else four; very long sums are split over the
   //    grid too, which costs a summing launch (about 5 us);
-  //  - long sums: 64x32 tiles of four waves (2048 x 512 x 3072: 107 us, 32x32
-  //    tiles of four waves 112 us);
+  //  - long sums: 64x32 tiles of four waves once there are two for each compute
+  //    unit (2048 x 512 x 3072: 106 us, 32x32 tiles of four waves 111 us), before
+  //    that 32x32 ones (1200 x 280 x 1680: 33 against 43 us, 1600 x 400 x 2400:
+  //    66 against 76 us; FP32 36 against 44 us);
   //  - short sums: four waves a 32x32 tile while there are fewer tiles than
   //    SIMDs (768 x 512 x 128: 7.2 us, one wave 8.3 us), one wave then
   //    (1536 x 1000 x 256: 21.5 us, four waves 24.4 us), and 32x64 tiles once
@@ -548,7 +550,7 @@ bool direct_dispatch(Ctx* c, const GemmArgs& g) {
   if (t32 <= 320) {
     if (steps >= 16) go(I2(), I2(), I8(), I2());
     else go(I2(), I2(), I4(), I2());
-  } else if (t32 < 4096 && steps >= 64) {
+  } else if (t32 >= 900 && t32 < 4096 && steps >= 64) {
     go(I4(), I2(), I4(), I1());
   } else if (t32 < 1024) {
     go(I2(), I2(), I4(), I2());

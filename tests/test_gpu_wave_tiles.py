@@ -111,3 +111,16 @@ def test_infinite_entry_stays_in_its_rows(ctx):
     keep = np.arange(ml) != 5
     assert not np.isfinite(o[5]).any()
     assert rel(o[keep], ref[keep]) < 1e-12
+
+
+@pytest.mark.parametrize("ml, d, mr, wl, wr", [(1, 2, 3, 2, 3), (31, 2, 17, 3, 5), (32, 3, 20, 1, 1), (33, 4, 24, 6, 6),
+                                               (64, 1, 16, 4, 4), (97, 2, 9, 5, 3)])
+def test_mpo_adjoint(ctx, ml, d, mr, wl, wr):
+    """Wbar summed over the left bond, at bonds and entry counts that do and do
+    not divide its split."""
+    from oracle.adjoint import heff_grad_W
+    (L, W, R, psi), (Ld, Wd, Rd, pd) = inputs(ml, d, mr, wl, wr, torch.float64)
+    ybar = synth.gaussian((ml, d, mr), 77)
+    out = torch.empty(wl, wr, d, d, dtype=torch.float64, device=DEV)
+    ctx.heff_grad_W(Ld, Rd, pd, torch.tensor(ybar, device=DEV), out)
+    assert rel(out.cpu().numpy(), heff_grad_W(L, R, psi, ybar)) < 1e-12
