@@ -231,6 +231,10 @@ void gram_schmidt(Ctx* c, const double* V, long ldv, int k, const int* kdev, dou
 // unless k+1 = kk; ab[2k] = c1[k] + c2[k], ab[2k+1] = beta (device or pinned host memory)
 void lanczos_tail(Ctx* c, const double* w, long n, const double* npart, const double* c1, const double* c2, int k,
                   const int* kdev, int kk, double* V, double* ab);
+// Both in one launch where the rows V_0 .. V_k and w fit one workgroup's
+// registers (48 rows up to n = 1024, 24 up to 2048, 12 up to 4096); false:
+// they do not, nothing was launched.  w is left as it is.
+bool lanczos_ortho(Ctx* c, double* V, long n, int k, int kk, const double* w, double* ab);
 // dst = V_k, *kcur = k with k = *knext
 void copy_row_f64(Ctx* c, const double* V, long n, const int* knext, int* kcur, double* dst);
 void set_int_dev(Ctx* c, int* p, int v);                                             // *p = v

@@ -413,7 +413,10 @@ __device__ __forceinline__ double wave_row_sums(const double* acc) {
       const bool up = (lane & off) != 0;
 #pragma unroll
       for (int j = 0; j < h; ++j) {
-        const double mine = up ? v[j + h] : v[j], give = up ? v[j] : v[j + h];
+        double a = v[j], b = v[j + h];
+        // else the choice becomes an index, and that a chain of P choices
+        asm volatile("" : "+v"(a), "+v"(b));
+        const double mine = up ? b : a, give = up ? a : b;
         v[j] = mine + __shfl_xor(give, off, 64);
       }
     } else {
@@ -486,8 +489,8 @@ __device__ __forceinline__ void load_coefs(double* sc, int rows, double* coef, c
 // the latency of one turn for short vectors and by L2 / HBM for long ones.
 // Measured, MODE 0 / 1 / 2, about 20 rows: n = 61440 4.2 / 6.7 / 5.8 us (a
 // thread per element with all rows in every wave, 64 workgroups: 15 / 12 / 8.5
-// us and two launches of 4 us for the sums), n = 2048 3.5 / 4.3 / 3.4 us (8.2 /
-// 8.2 / 4.4 us and the two launches).
+// us and two launches of 4 us for the sums; since then 4.1 / 5.2 / 4.8 us),
+// n = 2048 3.5 / 4.3 / 3.4 us (8.2 / 8.2 / 4.4 us and the two launches).
 constexpr int kGsChunk = kThreads;
 typedef double d2u __attribute__((ext_vector_type(2), aligned(8)));
 
@@ -611,6 +614,114 @@ void lanczos_tail_kernel(const double* __restrict__ w, long n, const double* __r
   const double f = (b > 0.0) ? 1.0 / b : 0.0;
   for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x)
     vnext[i] = w[i] * f;
+}
+
+// Gram-Schmidt twice and the end of a Lanczos step, as the passes and the tail
+// above, for short vectors and few rows: one workgroup keeps V, E elements of
+// up to KR rows a thread, in registers from the first sums to the last update.
+// Bound by the load of V through one compute unit (64 bytes a clock) and the
+// latency of the three sums; it saves three launches.  Up to 8 / 16 / 24 / 48
+// rows it takes 3.8 / 5.3 / 7.2 / 12.3 us for n <= 1024 and 4.8 / 7.0 / 9.4 us
+// for n <= 2048, where the four launches take 13 to 15 us and their gaps.
+constexpr int kOrthoThreads = 512;
+
+template <int E, int KR>
+__global__ __launch_bounds__(kOrthoThreads)
+void lanczos_ortho_kernel(double* __restrict__ V, long n, int k, int kk, const double* __restrict__ w,
+                          double* __restrict__ ab) {
+  constexpr int NW = kOrthoThreads / 64;
+  static_assert(KR % 8 == 0, "rows are summed eight at a time");
+  __shared__ double sp[NW][KR], sc[KR], sn[NW];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, rows = k + 1;
+  auto at = [&](int q) { return 2L * (threadIdx.x + kOrthoThreads * q); };     // pair q of the thread
+  // no branches: every load is a pair within the row.  An odd row's last
+  // element is the second of a pair whose first belongs to another thread; x is
+  // zero where the thread has no element, V whatever was loaded
+  auto load = [&](const double* p, double (&v)[E]) {
+#pragma unroll
+    for (int q = 0; q < E / 2; ++q) {
+      const d2u a = *reinterpret_cast<const d2u*>(p + min(at(q), n - 2));
+      v[2 * q] = a.x;
+      v[2 * q + 1] = a.y;
+    }
+  };
+  double x[E], v[KR][E];
+  auto cut = [&]() {
+#pragma unroll
+    for (int q = 0; q < E / 2; ++q) {
+      x[2 * q] = at(q) < n - 1 ? x[2 * q] : 0.0;
+      x[2 * q + 1] = at(q) < n ? x[2 * q + 1] : 0.0;
+    }
+  };
+  load(w, x);
+#pragma unroll
+  for (int j = 0; j < KR; ++j) load(V + (long)min(j, rows - 1) * n, v[j]);
+  cut();
+  double alpha = 0.0;
+  auto sums = [&](auto gt) {             // rows 8 g .. 8 g + 7
+    constexpr int g = 8 * decltype(gt)::value;
+    if constexpr (g < KR) {
+      double acc[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        acc[j] = 0.0;
+#pragma unroll
+        for (int e = 0; e < E; ++e) acc[j] += v[g + j][e] * x[e];
+      }
+      const double t = wave_row_sums<8>(acc);
+      if (lane % 8 == 0) sp[wave][g + lane / 8] = t;
+    }
+  };
+  auto pass = [&]() {
+    static_assert(KR <= 48, "six groups of rows");
+    sums(std::integral_constant<int, 0>());
+    sums(std::integral_constant<int, 1>());
+    sums(std::integral_constant<int, 2>());
+    sums(std::integral_constant<int, 3>());
+    sums(std::integral_constant<int, 4>());
+    sums(std::integral_constant<int, 5>());
+    __syncthreads();
+    if (threadIdx.x < KR) {
+      double s = 0.0;
+#pragma unroll
+      for (int q = 0; q < NW; ++q) s += sp[q][threadIdx.x];
+      sc[threadIdx.x] = (int)threadIdx.x < rows ? s : 0.0;     // the rows past the last are copies of it
+    }
+    __syncthreads();
+    alpha += sc[k];
+#pragma unroll
+    for (int j = 0; j < KR; ++j) {
+      const double c = sc[j];
+#pragma unroll
+      for (int e = 0; e < E; ++e) x[e] -= c * v[j][e];
+    }
+    cut();
+  };
+  pass();
+  pass();
+  double s = 0.0;
+#pragma unroll
+  for (int e = 0; e < E; ++e) s += x[e] * x[e];
+  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+  if (lane == 0) sn[wave] = s;
+  __syncthreads();
+  s = 0.0;
+#pragma unroll
+  for (int q = 0; q < NW; ++q) s += sn[q];
+  const double b = sqrt(fmax(s, 0.0));
+  if (threadIdx.x == 0) {
+    ab[2 * k] = alpha;
+    ab[2 * k + 1] = b;
+  }
+  if (rows >= kk) return;
+  double* vnext = V + (long)rows * n;
+  const double f = (b > 0.0) ? 1.0 / b : 0.0;
+#pragma unroll
+  for (int q = 0; q < E / 2; ++q) {
+    const long i = at(q), ic = min(i, n - 2);
+    if (i < n - 1) vnext[ic] = x[2 * q] * f;
+    if (i < n) vnext[ic + 1] = x[2 * q + 1] * f;
+  }
 }
 
 // dst = V_k and *kcur = k, k = *knext
@@ -898,6 +1009,37 @@ void lanczos_tail(Ctx* c, const double* w, long n, const double* npart, const do
   hipLaunchKernelGGL(lanczos_tail_kernel, dim3(grid_for(n)), dim3(kThreads), 0, c->stream, w, n, npart,
                      gs_blocks(n), c1, c2, k, kdev, kk, V, ab);
   D3S_HIP(hipGetLastError());
+}
+
+bool lanczos_ortho(Ctx* c, double* V, long n, int k, int kk, const double* w, double* ab) {
+  auto go = [&](auto e, auto kr) {
+    hipLaunchKernelGGL((lanczos_ortho_kernel<decltype(e)::value, decltype(kr)::value>), dim3(1), dim3(kOrthoThreads), 0,
+                       c->stream, V, n, k, kk, w, ab);
+    D3S_HIP(hipGetLastError());
+    return true;
+  };
+  using E2 = std::integral_constant<int, 2>;
+  using E4 = std::integral_constant<int, 4>;
+  using E8 = std::integral_constant<int, 8>;
+  using K8 = std::integral_constant<int, 8>;
+  using K16 = std::integral_constant<int, 16>;
+  using K24 = std::integral_constant<int, 24>;
+  using K48 = std::integral_constant<int, 48>;
+  const int rows = k + 1;
+  if (n < 2) return false;
+  if (n <= 2 * kOrthoThreads) {
+    if (rows <= 8) return go(E2(), K8());
+    if (rows <= 16) return go(E2(), K16());
+    if (rows <= 24) return go(E2(), K24());
+    if (rows <= 48) return go(E2(), K48());
+  } else if (n <= 4 * kOrthoThreads) {
+    if (rows <= 8) return go(E4(), K8());
+    if (rows <= 16) return go(E4(), K16());
+    if (rows <= 24) return go(E4(), K24());
+  } else if (n <= 8 * kOrthoThreads) {
+    if (rows <= 8) return go(E8(), K8());
+  }
+  return false;
 }
 
 void copy_row_f64(Ctx* c, const double* V, long n, const int* knext, int* kcur, double* dst) {

@@ -768,6 +768,7 @@ LanczosResult lanczos_core(Ctx* c, Matvec& mv, double* x, long n, double tol, in
       lanczos_tail(c, w, n, npart, cf1, cf2, 0, kdev, kk, V, ab);
     } else {
       mv.product(V + (long)k * n, w, use_f64);
+      if (lanczos_ortho(c, V, n, k, kk, w, ab)) return;
       gram_schmidt(c, V, n, k + 1, nullptr, w, n, cf1, cf2, npart, nullptr);
       lanczos_tail(c, w, n, npart, cf1, cf2, k, nullptr, kk, V, ab);
     }

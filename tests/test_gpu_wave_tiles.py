@@ -124,3 +124,31 @@ def test_mpo_adjoint(ctx, ml, d, mr, wl, wr):
     out = torch.empty(wl, wr, d, d, dtype=torch.float64, device=DEV)
     ctx.heff_grad_W(Ld, Rd, pd, torch.tensor(ybar, device=DEV), out)
     assert rel(out.cpu().numpy(), heff_grad_W(L, R, psi, ybar)) < 1e-12
+
+
+@pytest.mark.parametrize("ml, d, mr", [(1, 2, 1), (3, 1, 1), (5, 2, 3), (31, 2, 16), (341, 1, 3), (32, 4, 8), (41, 5, 5), (63, 1, 65),
+                                       (32, 2, 32), (683, 1, 3), (64, 1, 64), (17, 1, 241)])
+@pytest.mark.parametrize("kmax", [8, 17, 60])
+def test_lanczos_short_vectors(ctx, ml, d, mr, kmax):
+    """Vectors from 2 to 4097 elements and 8 to 60 Krylov vectors, across the
+    sizes at which the one-workgroup Gram-Schmidt changes its registers or ends:
+    the Ritz pair satisfies the eigenvalue equation to the requested 1e-11 of
+    the norm, ten times that for the restarts' accumulated rounding."""
+    rng = np.random.default_rng(ml * mr)
+    w = 3
+    sym = lambda x: (x + x.transpose(2, 1, 0)) / 2
+    L, R = sym(rng.standard_normal((ml, w, ml))), sym(rng.standard_normal((mr, w, mr)))
+    W = rng.standard_normal((w, w, d, d))
+    W = (W + W.transpose(0, 1, 3, 2)) / 2
+    x = torch.tensor(rng.standard_normal((ml, d, mr)), device=DEV)
+    th, nmv, ok = ctx.lanczos(*(torch.tensor(a, device=DEV) for a in (L, W, R)), x, tol=1e-11, kmax=kmax,
+                              max_matvecs=4000)
+    v = x.cpu().numpy()
+    hv = C.apply_heff(L, W, R, v)
+    norm = np.abs(th)
+    assert ok and abs(np.linalg.norm(v) - 1) < 1e-12
+    assert np.linalg.norm(hv - th * v) <= 1e-10 * max(1.0, norm)
+    if v.size <= 512:
+        H = C.heff_matrix(L, W, R)
+        ref = np.linalg.eigvalsh((H + H.T) / 2)[0]
+        assert abs(th - ref) <= 1e-10 * max(1.0, norm)
