@@ -110,8 +110,8 @@ d3s_status d3s_set_autotune(d3s_ctx ctx, int enable, const char* cache_path);
  * truncation (FP64): kind 1 = rocSOLVER divide and conquer (syevd), 2 =
  * rocSOLVER Jacobi (syevj), 3 = the library's own solver (Householder
  * tridiagonalisation and divide and conquer) for n <= 96 (one workgroup per
- * matrix, one launch: a single n = 64 matrix takes 0.25 ms, by syevd 2.1 ms)
- * and for a single matrix of n <= 1024 (n = 512: 2.4 ms, by syevd 11.3 ms),
+ * matrix, one launch: a single n = 64 matrix takes 0.18 ms, by syevd 2.1 ms)
+ * and for a single matrix of n <= 1024 (n = 512: 2.3 ms, by syevd 11.2 ms),
  * syevd otherwise, 0 = Jacobi for sizes <= jacobi_max_n and as kind 3 above (the
  * default, with jacobi_max_n 0).  All give the eigenpairs to FP64 accuracy
  * (eigenvectors of repeated eigenvalues may differ by a rotation within

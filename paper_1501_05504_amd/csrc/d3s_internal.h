@@ -232,7 +232,7 @@ void gram_schmidt(Ctx* c, const double* V, long ldv, int k, const int* kdev, dou
 void lanczos_tail(Ctx* c, const double* w, long n, const double* npart, const double* c1, const double* c2, int k,
                   const int* kdev, int kk, double* V, double* ab);
 // Both in one launch where the rows V_0 .. V_k and w fit one workgroup's
-// registers (48 rows up to n = 1024, 24 up to 2048, 12 up to 4096); false:
+// registers (48 rows up to n = 1024, 24 up to 2048, 8 up to 4096); false:
 // they do not, nothing was launched.  w is left as it is.
 bool lanczos_ortho(Ctx* c, double* V, long n, int k, int kk, const double* w, double* ab);
 // dst = V_k, *kcur = k with k = *knext
@@ -557,7 +557,7 @@ void syevd_batched_f64(Ctx* c, int n, int batch, double* A, double* evals);
 // The batched eigensolver of the truncations: the library's own (eigsmall.hip)
 // up to n = kEigSmallMax with eigensolver kinds 0 and 3, rocSOLVER otherwise.
 // The bound is the register and LDS space of one workgroup, not speed: at
-// n = 96 the own solver takes 0.49 ms for up to 256 matrices, syevd 1.6 ms for
+// n = 96 the own solver takes 0.34 ms for up to 256 matrices, syevd 1.6 ms for
 // one.  eig_small_launch only launches: info[b] (device) is 0, 1 (not
 // converged) or 2 (non-finite input).
 constexpr int kEigSmallMax = 96;
@@ -567,7 +567,7 @@ void eig_small_check(const int* info, int batch);
 // One matrix of kEigSmallMax < n <= kEigMidMax over the whole device
 // (eigmid.hip); only launches, as above; false: no memory for its scratch,
 // nothing was launched.  Up to the size whose row fits a wave's registers; at
-// n = 128 / 512 / 1024 it takes 0.6 / 2.4 / 7.0 ms, syevd 2.2 / 11.3 / 22.5.
+// n = 128 / 512 / 1024 it takes 0.45 / 2.3 / 6.8 ms, syevd 2.1 / 11.2 / 22.3.
 // Several matrices stay with syevd, whose launches a batch shares.
 constexpr int kEigMidMax = 1024;
 bool eig_mid_used(const Ctx* c, int n, int batch);

@@ -51,8 +51,15 @@ __device__ __forceinline__ double rsqrt_f64(double x) {
   return fma(y * e, fma(0.375, e, 0.5), y);
 }
 
+// 1 / x for normal x: the hardware estimate and two Newton steps, within an ulp
+__device__ __forceinline__ double rcp_f64(double x) {
+  double y = __builtin_amdgcn_rcp(x);
+  y = fma(fma(-x, y, 1.0), y, y);
+  return fma(fma(-x, y, 1.0), y, y);
+}
+
 constexpr double kUlp = 2.220446049250313e-16;
-constexpr int kLeaf = 16;
+constexpr int kLeaf = 4;
 
 // Implicit QL with shifts on the tridiagonal block of size m <= kLeaf at d, e
 // by one wave; the block's eigenvectors (its rows and columns of w, identity
@@ -147,7 +154,7 @@ __device__ void secular_root(const double* d, const double* z2, int k, int j, do
   for (int it = 0; it < 80; ++it) {
     double a1 = 0.0, b1 = 0.0, a2 = 0.0, b2 = 0.0;
     for (int i = part; i < k; i += L) {
-      const double r = 1.0 / ((d[i] - d0) - tau), t = z2[i] * r;
+      const double r = rcp_f64((d[i] - d0) - tau), t = z2[i] * r;
       if (i <= j) {
         a1 += t;
         b1 = fma(t, r, b1);
@@ -183,72 +190,76 @@ __device__ void secular_root(const double* d, const double* z2, int k, int j, do
 // Householder reduction of a symmetric matrix of size n <= NMAX to tridiagonal
 // form by a workgroup of kLanes NMAX threads; thread (row, part) holds elements
 // (row, part + kLanes j) in a.  Step k annihilates column k below the
-// subdiagonal with H = 1 - tau v v^T: v is row k of sV right of the diagonal,
-// its first entry sV0[k].
+// subdiagonal with H = 1 - tau v v^T: v is row k of sV, zero up to column k.
+// sX: NMAX + 1 entries for the subdiagonal entry of the column at hand.
 template <int NMAX>
-__device__ void reduce_tridiagonal(double (&a)[NMAX / kLanes], int n, double* sV, double* sV0, double* sTau, double* sP,
+__device__ void reduce_tridiagonal(double (&a)[NMAX / kLanes], int n, double* sV, double* sX, double* sTau, double* sP,
                                    double* d, double* e) {
   constexpr int E = NMAX / kLanes;
   constexpr int LD = NMAX + 1;
   const int tid = threadIdx.x, lane = tid & 63;
   const int row = tid / kLanes, part = tid % kLanes;
-  auto put_column = [&](int k) {        // column k of the matrix into row k of sV
+  // column k: its diagonal entry to d, the next to sX, the others to row k of
+  // sV, which is zero elsewhere
+  auto put_column = [&](int k) {
     double t = a[0];
 #pragma unroll
     for (int j = 1; j < E; ++j) {
       t = j == k / kLanes ? a[j] : t;
       loaded(t);                        // else the array goes to memory for an indexed read
     }
-    if (part == k % kLanes) sV[k * LD + row] = t;
+    if (part == k % kLanes) {
+      sV[k * LD + row] = (row > k + 1 && row < n) ? t : 0.0;
+      if (row == k) d[k] = t;
+      if (row == k + 1) sX[k] = t;
+    }
   };
+  // rows whose wave is done are no longer stored: zero from here on
+  for (int i = tid; i < NMAX * LD; i += kLanes * NMAX) sV[i] = 0.0;
+  if (part == 0) sP[row] = 0.0;
+  __syncthreads();
   put_column(0);
   __syncthreads();
   for (int k = 0; k < n - 2; ++k) {
-    const double* x = sV + k * LD;
-    const bool busy = (tid | 63) / kLanes > k;         // the wave still has a row below row k
-    double v0 = 0.0, tau = 0.0, p = 0.0, vc[E];
-    auto v_of = [&](int c, double t) {                 // entry c of v, t = x[c]
-      t = c == k + 1 ? v0 : t;
-      return c > k ? t : 0.0;
-    };
+    double* x = sV + k * LD;
+    const bool busy = (tid | 63) / kLanes >= k;        // below, the wave's rows and sP are done
+    double tau = 0.0, p = 0.0, vc[E];
     if (busy) {
-#pragma unroll
-      for (int j = 0; j < E; ++j) vc[j] = x[part + kLanes * j];
-#pragma unroll
-      for (int j = 0; j < E; ++j) loaded(vc[j]);
+      const double x0 = sX[k];
       double s2 = 0.0;
 #pragma unroll
       for (int i = 0; i < (NMAX + 63) / 64; ++i) {
         const int r = lane + 64 * i;
         double t = x[min(r, NMAX - 1)];
         loaded(t);
-        t = (r > k + 1 && r < n) ? t : 0.0;
+        t = (r == k + 1 || r >= NMAX) ? 0.0 : t;       // another wave may have stored v's entry
         s2 = fma(t, t, s2);
       }
       s2 = sum64(s2);
-      const double x0 = x[k + 1];
-      double ek = x0;
+      double v0 = 0.0, ek = x0;
       if (s2 > 0.0) {
         ek = -copysign(sqrt(fma(x0, x0, s2)), x0);
         v0 = x0 - ek;
         tau = 2.0 / fma(v0, v0, s2);
       }
+      x[k + 1] = v0;                                   // every wave, the same value: no barrier
       if (tid == kLanes * NMAX - 1) {
-        d[k] = x[k];
         e[k] = ek;
         sTau[k] = tau;
-        sV0[k] = v0;
       }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
 #pragma unroll
-      for (int j = 0; j < E; ++j) vc[j] = v_of(part + kLanes * j, vc[j]);   // columns up to k are done: zero
+      for (int j = 0; j < E; ++j) vc[j] = x[part + kLanes * j];
 #pragma unroll
       for (int j = 0; j < E; ++j) p = fma(a[j], vc[j], p);
       p = tau * sum8(p);
-      if (part == 0) sP[row] = (row > k && row < n) ? p : 0.0;
+      p = (row > k && row < n) ? p : 0.0;
+      if (part == 0) sP[row] = p;
     }
     __syncthreads();
     if (busy) {
-      double wc[E], pv = 0.0, vr = x[min(row, NMAX - 1)];
+      double wc[E], pv = 0.0;
+      const double vr = x[row];
 #pragma unroll
       for (int j = 0; j < E; ++j) wc[j] = sP[part + kLanes * j];
 #pragma unroll
@@ -257,35 +268,24 @@ __device__ void reduce_tridiagonal(double (&a)[NMAX / kLanes], int n, double* sV
         double pr = sP[rc], xr = x[rc];
         loaded(pr);
         loaded(xr);
-        pv = fma(r < n ? pr : 0.0, v_of(r, xr), pv);
+        pv = fma(r < NMAX ? pr : 0.0, xr, pv);
       }
-#pragma unroll
-      for (int j = 0; j < E; ++j) loaded(wc[j]);
-      loaded(vr);
       const double kk = 0.5 * tau * sum64(pv);
-      vr = row < n ? v_of(row, vr) : 0.0;
-      const double wr = (row > k ? p : 0.0) - kk * vr;
+      const double wr = p - kk * vr;
 #pragma unroll
       for (int j = 0; j < E; ++j) {
-        wc[j] = part + kLanes * j > k ? fma(-kk, vc[j], wc[j]) : 0.0;
+        wc[j] = fma(-kk, vc[j], wc[j]);
         a[j] -= fma(vr, wc[j], wr * vc[j]);
       }
       put_column(k + 1);
     }
     __syncthreads();
   }
-  // the last two diagonal entries and the last off-diagonal one
+  // the last diagonal entry, and for n = 2 .. the last off-diagonal one
   if (n >= 2) {
-    if (n == 2) put_column(0);
     put_column(n - 1);
     __syncthreads();
-    if (tid == 0) {
-      d[n - 2] = sV[(n - 2) * LD + n - 2];
-      e[n - 2] = sV[(n - 2) * LD + n - 1];
-      d[n - 1] = sV[(n - 1) * LD + n - 1];
-    }
-  } else if (tid == 0) {
-    d[0] = sV[0];
+    if (tid == 0) e[n - 2] = sX[n - 2];
   }
 }
 
@@ -293,10 +293,11 @@ __device__ void reduce_tridiagonal(double (&a)[NMAX / kLanes], int n, double* sV
 template <int NMAX>
 struct TridiagDc {
   static constexpr int LD = NMAX + 1;
+  static constexpr int kMerges = NMAX <= 32 ? 4 : (NMAX <= 64 ? 8 : 16);    // of the first level
   double w[NMAX * LD];                  // eigenvectors, column j belongs to d[j]
   double d[NMAX + 1], e[NMAX + 1];      // diagonal (eigenvalues on return) and off-diagonal
   double zv[NMAX], ds[NMAX], zs[NMAX], zh[NMAX], tau[NMAX], dummy[kLanes * NMAX / 64][kLeaf + 1];
-  int order[NMAX], list[NMAX], org[NMAX], rotp[NMAX], rotn[NMAX], nlist[kLanes], nrot[kLanes], bad, close;
+  int order[NMAX], list[NMAX], org[NMAX], rotp[NMAX], rotn[NMAX], nlist[kMerges], nrot[kMerges], bad, close;
 };
 
 // Eigenpairs of the tridiagonal matrix S.d, S.e of size n <= NMAX by a
@@ -323,9 +324,9 @@ __device__ int tridiag_dc(TridiagDc<NMAX>& S, int n) {
   int levels = 0;
   while ((n >> levels) >= kLeaf + (((n >> levels) << levels) == n ? 1 : 0)) ++levels;
   const int nleaf = 1 << levels;
-  auto bound = [&](int i, int count) { return (int)((long)n * i / count); };
+  auto bound = [&](int i, int lg) { return (n * i) >> lg; };      // part i of 2^lg
   if (tid > 0 && tid < nleaf) {
-    const int b = bound(tid, nleaf);
+    const int b = bound(tid, levels);
     const double c = fabs(e[b - 1]);
     d[b - 1] -= c;                       // leaves have two entries or more: no overlap
     d[b] -= c;
@@ -340,17 +341,17 @@ __device__ int tridiag_dc(TridiagDc<NMAX>& S, int n) {
   __syncthreads();                       // d is written from here on
   if (!isfinite(total)) return 2;        // the same for every thread
   const double tol = 8.0 * kUlp * tnorm;
-  if (wave < nleaf) {
-    const int b = bound(wave, nleaf), m = bound(wave + 1, nleaf) - b;
+  for (int leaf = wave; leaf < nleaf; leaf += NT / 64) {
+    const int b = bound(leaf, levels), m = bound(leaf + 1, levels) - b;
     if (!ql_leaf(d + b, e + b, m, sW + b * LD + b, LD, S.dummy[wave]) && lane == 0) bad = 1;
   }
   __syncthreads();
   // ---- merges, all pairs of a level side by side.  Groups of eight lanes: of
   // column `row`, of the sorted list's entry, and of a root in turn
-  for (int cnt = nleaf / 2; cnt >= 1; cnt /= 2) {
+  for (int lg = levels - 1; lg >= 0; --lg) {
     int b = 0;                           // the block of this group's column
-    while (b + 1 < cnt && row >= bound(b + 1, cnt)) ++b;
-    const int lo = bound(b, cnt), hi = row < n ? bound(b + 1, cnt) : lo, mid = bound(2 * b + 1, 2 * cnt);
+    while (b + 1 < (1 << lg) && row >= bound(b + 1, lg)) ++b;
+    const int lo = bound(b, lg), hi = row < n ? bound(b + 1, lg) : lo, mid = bound(2 * b + 1, lg + 1);
     const double beta = e[mid - 1], rho = 2.0 * fabs(beta);
     const bool in = row < n;
     // coupling vector (unit norm) and ascending order within the block
@@ -366,7 +367,7 @@ __device__ int tridiag_dc(TridiagDc<NMAX>& S, int n) {
         order[r] = row;
       }
     }
-    if (tid < kLanes) nrot[tid] = 0;
+    if (tid < TridiagDc<NMAX>::kMerges) nrot[tid] = 0;
     if (tid == 0) close = 0;
     __syncthreads();
     // entries that couple too weakly keep their eigenpair; the others form the
@@ -394,16 +395,24 @@ __device__ int tridiag_dc(TridiagDc<NMAX>& S, int n) {
     __syncthreads();
     if (close) {                         // one lane per block walks its list
       if (in && part == 0 && row == lo && nlist[b] > 0) {
-        int k = 0, nr = 0, p = list[lo];
-        for (int i = 1; i < nlist[b]; ++i) {
-          const int q = list[lo + i];
-          const double zp = zv[p], zq = zv[q], t = hypot(zp, zq), c = zq / t, s = -zp / t;
-          if (fabs((d[q] - d[p]) * c * s) <= tol) {
-            const double dp = d[p], dq = d[q];
-            zv[q] = t;
-            zv[p] = 0.0;
-            d[p] = dp * c * c + dq * s * s;
-            d[q] = dp * s * s + dq * c * c;
+        const int cnt = nlist[b];
+        int k = 0, nr = 0, p = list[lo], nq = list[lo + min(1, cnt - 1)];
+        double dp = d[p], zp = zv[p], nd = d[nq], nz = zv[nq];
+        for (int i = 1; i < cnt; ++i) {
+          const int q = nq;
+          double dq = nd, zq = nz;
+          nq = list[lo + min(i + 1, cnt - 1)];       // read ahead
+          nd = d[nq];
+          nz = zv[nq];
+          const double h = zp * zp + zq * zq;
+          if (fabs((dq - dp) * zp * zq) <= tol * h) {
+            const double r = rsqrt_f64(h), c = zq * r, s = -zp * r, x = dp;
+            dp = x * c * c + dq * s * s;
+            dq = x * s * s + dq * c * c;
+            zq = h * r;
+            zv[q] = zq;
+            d[p] = dp;
+            d[q] = dq;
             rotp[lo + nr] = p;
             rotn[lo + nr] = q;
             ds[lo + nr] = c;
@@ -413,6 +422,8 @@ __device__ int tridiag_dc(TridiagDc<NMAX>& S, int n) {
             list[lo + k++] = p;
           }
           p = q;
+          dp = dq;
+          zp = zq;
         }
         list[lo + k++] = p;
         nlist[b] = k;
@@ -421,12 +432,20 @@ __device__ int tridiag_dc(TridiagDc<NMAX>& S, int n) {
       __syncthreads();
       if (in && part == 0) {             // row `row` of the block
         double* w = sW + row * LD;
+        int held = -1;                   // column of the value y, not stored yet
+        double y = 0.0;
         for (int i = 0; i < nrot[b]; ++i) {
           const int p = rotp[lo + i], q = rotn[lo + i];
-          const double c = ds[lo + i], s = zs[lo + i], x = w[p], y = w[q];
-          w[p] = fma(c, x, s * y);
-          w[q] = fma(c, y, -(s * x));
+          const double c = ds[lo + i], s = zs[lo + i], v = w[q];
+          if (held != p) {
+            if (held >= 0) w[held] = y;
+            y = w[p];
+          }
+          w[p] = fma(c, y, s * v);
+          y = fma(c, v, -(s * y));
+          held = q;
         }
+        if (held >= 0) w[held] = y;
       }
       __syncthreads();
     }
@@ -463,19 +482,30 @@ __device__ int tridiag_dc(TridiagDc<NMAX>& S, int n) {
     double out[E];
     if (active) {
       const double dj = ds[lo + o];
-      double nn = 0.0;
-      for (int i = part; i < k; i += kLanes) {
-        const double t = zh[lo + i] / ((ds[lo + i] - dj) - tj);
-        nn = fma(t, t, nn);
+      double nn = 0.0, tv[E];            // entry part + 8 m of the rank-one update's vector
+#pragma unroll
+      for (int m = 0; m < E; ++m) {
+        const int i = part + kLanes * m;
+        tv[m] = 0.0;
+        if (i < k) tv[m] = zh[lo + i] / ((ds[lo + i] - dj) - tj);
+        nn = fma(tv[m], tv[m], nn);
       }
       const double f = 1.0 / sqrt(sum8(nn));
 #pragma unroll
       for (int q = 0; q < E; ++q) out[q] = 0.0;
-      for (int i = 0; i < k; ++i) {
-        const double t = f * (zh[lo + i] / ((ds[lo + i] - dj) - tj));
-        const double* w = sW + (lo + part) * LD + list[lo + i];
+      const double* w0 = sW + (lo + part) * LD;
 #pragma unroll
-        for (int q = 0; q < E; ++q) out[q] = fma(t, w[min(q * kLanes, NMAX - 1 - lo - part) * LD], out[q]);
+      for (int m = 0; m < E; ++m) {
+        if (kLanes * m >= k) break;
+        tv[m] *= f;
+#pragma unroll 2
+        for (int s = 0; s < kLanes; ++s) {
+          const int i = min(kLanes * m + s, k - 1);
+          const double t = __shfl(tv[m], (lane & ~(kLanes - 1)) + s, 64);     // zero past k
+          const double* w = w0 + list[lo + i];
+#pragma unroll
+          for (int q = 0; q < E; ++q) out[q] = fma(t, w[min(q * kLanes, NMAX - 1 - lo - part) * LD], out[q]);
+        }
       }
     }
     __syncthreads();

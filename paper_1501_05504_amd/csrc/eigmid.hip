@@ -17,9 +17,9 @@
 //    the rank-one update, and one product per half with the vectors so far.
 //  - Back-transformation: a wave holds an eigenvector in registers and applies
 //    the reflections in turn (two to a wave: 209 instead of 128 us at n = 512).
-// A matrix of n = 512 takes 2.4 ms, of which the columns 1.7 ms at 4 us, the
-// tail 0.2, the tridiagonal problem 0.35 and the way back 0.13; syevd takes
-// 11.3 ms.
+// A matrix of n = 512 takes 2.3 ms, of which the columns 1.7 ms at 4 us, the
+// tail 0.13, the tridiagonal problem 0.3 and the way back 0.13; syevd takes
+// 11.2 ms.
 #include "d3s_internal.h"
 #include "eigdc.h"
 
@@ -135,7 +135,7 @@ __global__ __launch_bounds__(kLanes * kTail)
 void reduce_tail_kernel(const double* __restrict__ A, int n, double* __restrict__ V, int ldv, const double* __restrict__ pin,
                         double* __restrict__ tauv, double* __restrict__ d, double* __restrict__ e) {
   constexpr int E = kTail / kLanes, LD = kTail + 1;
-  __shared__ double sV[kTail * LD], sP[kTail], sTau[kTail], sV0[kTail], sd[kTail + 1], se[kTail + 1];
+  __shared__ double sV[kTail * LD], sP[kTail], sTau[kTail], sX[kTail + 1], sd[kTail + 1], se[kTail + 1];
   const int tid = threadIdx.x, lane = tid & 63, row = tid / kLanes, part = tid % kLanes, K = n - kTail;
   const double* v = V + (long)(K - 1) * ldv + K;
   const double* p = pin + K;
@@ -152,11 +152,11 @@ void reduce_tail_kernel(const double* __restrict__ A, int n, double* __restrict_
   const double kk = 0.5 * tauv[K - 1] * sum64(s), vr = v[row], wr = p[row] - kk * vr;
 #pragma unroll
   for (int j = 0; j < E; ++j) a[j] -= fma(vr, pc[j] - kk * vc[j], wr * vc[j]);
-  reduce_tridiagonal<kTail>(a, kTail, sV, sV0, sTau, sP, sd, se);
+  reduce_tridiagonal<kTail>(a, kTail, sV, sX, sTau, sP, sd, se);
   __syncthreads();
   for (int i = tid; i < kTail * kTail; i += kLanes * kTail) {
     const int k = i / kTail, c = i % kTail;
-    if (k < kTail - 2 && c > k) V[(long)(K + k) * ldv + K + c] = c == k + 1 ? sV0[k] : sV[k * LD + c];
+    if (k < kTail - 2 && c > k) V[(long)(K + k) * ldv + K + c] = sV[k * LD + c];
   }
   if (tid < kTail) {
     d[K + tid] = sd[tid];

@@ -8,16 +8,22 @@
 //    eighth column each, so that a matrix-vector product is a few multiplies
 //    and three DPP additions; vectors shared by the rows go through LDS, and
 //    sums over a whole vector are formed by every wave for itself.
-//  - Tridiagonal eigenproblem: split into leaves of at most 16, each solved by
+//  - Tridiagonal eigenproblem: split into leaves of at most 4, each solved by
 //    one wave with the implicit QL iteration (its scalar recurrence, about 350
 //    cycles for each of about n^2 rotations, is why the whole matrix is not:
-//    that took 0.64 ms at n = 64), then merged in pairs by rank-one updates
+//    0.64 ms at n = 64), then merged in pairs by rank-one updates
 //    (Cuppen's method with deflation, the secular equation solved between the
 //    poles, and the coupling vector recomputed from the roots so that the
 //    vectors come out orthogonal, as Gu and Eisenstat showed).  Eight lanes
 //    share a root's sums.
 //  - Back-transformation: eight lanes hold an eigenvector and apply the
 //    Householder reflections in turn, without barriers.
+// Bound by the latency of these chains (n = 64, in thousands of cycles:
+// reduction 140, leaves 45, secular equations 47, vectors 27, back 23).  What
+// they are made of counts: values that are loaded or chosen under a condition
+// became branches that wait for every load in turn, and leaves of 16 took 144
+// thousand cycles.  One matrix, or up to 256: n = 32 0.09 ms, 64 0.18 ms, 96
+// 0.34 ms; the library solver takes 0.95, 2.1 and 1.5 ms for one.
 #include "d3s_internal.h"
 #include "eigdc.h"
 
@@ -33,7 +39,7 @@ void eig_small_kernel(double* __restrict__ A, double* __restrict__ evals, int n,
   constexpr int LD = NMAX + 1;
   constexpr int NT = kLanes * NMAX;
   __shared__ double sV[NMAX * LD];      // Householder vectors, row k
-  __shared__ double sP[NMAX], sTau[NMAX], sV0[NMAX];
+  __shared__ double sP[NMAX], sTau[NMAX], sX[NMAX + 1];
   __shared__ TridiagDc<NMAX> D;
   double *d = D.d, *e = D.e, *sW = D.w;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -64,7 +70,7 @@ void eig_small_kernel(double* __restrict__ A, double* __restrict__ evals, int n,
 #pragma unroll
   for (int j = 0; j < E; ++j) a[j] = ldexp(a[j], -scale);
   __syncthreads();                      // sP is written again
-  reduce_tridiagonal<NMAX>(a, n, sV, sV0, sTau, sP, d, e);
+  reduce_tridiagonal<NMAX>(a, n, sV, sX, sTau, sP, d, e);
   __syncthreads();
   const int bad = tridiag_dc<NMAX>(D, n);
   if (bad == 2) {                       // the same for every thread
@@ -83,17 +89,9 @@ void eig_small_kernel(double* __restrict__ A, double* __restrict__ evals, int n,
     for (int j = 0; j < E; ++j) a[j] = sW[(part + kLanes * j) * LD + row];
     for (int k = n - 3; k >= 0; --k) {
       const double* x = sV + k * LD;
-      const double v0 = sV0[k];
       double vc[E], y = 0.0;
 #pragma unroll
       for (int j = 0; j < E; ++j) vc[j] = x[part + kLanes * j];
-#pragma unroll
-      for (int j = 0; j < E; ++j) {
-        const int c = part + kLanes * j;
-        loaded(vc[j]);
-        vc[j] = c == k + 1 ? v0 : vc[j];
-        vc[j] = (c > k && c < n) ? vc[j] : 0.0;
-      }
 #pragma unroll
       for (int j = 0; j < E; ++j) y = fma(a[j], vc[j], y);
       y = sTau[k] * sum8(y);

@@ -140,9 +140,8 @@ void multi_gemm(Ctx* c, const std::vector<MTask>& ts, bool a_kc, bool b_kc, cons
 // per matrix, while below n = 96 its batched small-size path grows steeply
 // with the batch (n = 64, 40 matrices: 18 ms against 2 ms at n = 96).  The
 // library's own solver takes the small ones (one workgroup per matrix, one
-// launch; a batch of up to 256 takes 0.13 ms at n = 32, 0.25 ms at n = 64 and
-// 0.49 ms at n = 96).  Sizes are padded
-// (to a multiple of 8 for the own solver, else to at least 96 and a multiple
+// launch; a batch of up to 256 takes 0.09 ms at n = 32, 0.18 ms at n = 64 and
+// 0.34 ms at n = 96).  Sizes are padded (to a multiple of 8 for the own solver, else to at least 96 and a multiple
 // of 16; a lone matrix is not padded), sorted, and grouped contiguously with
 // the least modelled cost (dynamic programming).
 EigPlan plan_eig(Ctx* c, const std::vector<int>& n) {
@@ -170,7 +169,7 @@ EigPlan plan_eig(Ctx* c, const std::vector<int>& n) {
   auto cost = [&](int i, int j) {
     const int cnt = j - i + 1;
     const double np = pad(n[ord[j]], cnt);
-    if (small(n[ord[j]])) return (3e-5 + (np <= 64 ? 3.4e-6 : 4.8e-6) * np) * ((cnt + 255) / 256);
+    if (small(n[ord[j]])) return (3e-5 + (np <= 64 ? 2.3e-6 : 3.2e-6) * np) * ((cnt + 255) / 256);
     return col * np + 1.6e-12 * (double)cnt * np * np * np;
   };
   const int G = (int)ord.size();
