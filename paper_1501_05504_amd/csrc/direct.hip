@@ -376,7 +376,7 @@ void front_kernel(FParams p) {
   __shared__ __align__(16) S sT[4 * kLds > kTile ? 4 * kLds : kTile];
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int ld2 = p.ld2, d = 1 << ld2, wx = p.wx, am = p.am, wo = p.wo;
-  const int np = NC >> ld2;                          // B-side points per tile
+  const int lnp = (TN == 1 ? 6 : 7) - ld2, np = 1 << lnp;     // B-side points per tile
   const int nTm = (p.na + am - 1) / am, nTn = (p.nq + np - 1) / np;
   int tm, tn;
   tile_coords(nTm, nTn, tm, tn);
@@ -405,28 +405,38 @@ void front_kernel(FParams p) {
   for (int i = 0; i < MT; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = AV{0, 0, 0, 0};
+  // W[o][k], o = s*wo + v (L2R) or w*d + s (R2L), k = u*d + t, in fragments
+  // dealt to the waves; a wave's first kPre are on their way during the K loop
+  const S* Wg = reinterpret_cast<const S*>(p.W);
+  const int wr = R2L ? wx : wo, frags = mb * ks;
+  const float rks = 1.0f / ks, rwo = 1.0f / wo;      // quotients of small numbers
+  auto w_entry = [&](int f) {
+    const int m = (int)((f + 0.5f) * rks), o = min(m * 16 + lrow, nout - 1), k = min((f - m * ks) * 4 + g, kin - 1);
+    const int u = k >> ld2, t = k & (d - 1), os = (int)((o + 0.5f) * rwo);
+    const int w = R2L ? o >> ld2 : u, s = R2L ? o & (d - 1) : os, vv = R2L ? u : o - os * wo;
+    return Wg + ((((((w * wr + vv) << ld2) + s) << ld2)) + t);
+  };
+  auto put_w = [&](int f, S v) {
+    const int m = (int)((f + 0.5f) * rks);
+    sW[f * 64 + lane] = (m * 16 + lrow < nout && (f - m * ks) * 4 + g < kin) ? (S)p.alpha * v : S(0);
+  };
+  constexpr int kPre = 4;
+  S wpre[kPre];
+#pragma unroll
+  for (int q = 0; q < kPre; ++q) wpre[q] = *w_entry(min(wave + 4 * q, frags - 1));
   const int nfull = p.K / BK;
   mma_loop<S, MT, TN, true, R2L, 2>(acc, oa, ob, sT + wave * kLds, A, B, p.lda, p.ldb, nfull, 0, 1,
                                     p.K - nfull * BK);
-  // W[o][k], o = s*wo + v (L2R) or w*d + s (R2L), k = u*d + t
-  const S* Wg = reinterpret_cast<const S*>(p.W);
-  const int wr = R2L ? wx : wo;
-  for (int f = wave; f < mb * ks; f += 4) {
-    const int m = f / ks, o = m * 16 + lrow, k = (f - m * ks) * 4 + g;
-    S v = S(0);
-    if (o < nout && k < kin) {
-      const int u = k >> ld2, t = k & (d - 1);
-      const int w = R2L ? o >> ld2 : u, s = R2L ? o & (d - 1) : o / wo, vv = R2L ? u : o - s * wo;
-      v = (S)p.alpha * Wg[((((w * wr + vv) << ld2) + s) << ld2) + t];
-    }
-    sW[f * 64 + lane] = v;
-  }
+#pragma unroll
+  for (int q = 0; q < kPre; ++q)
+    if (wave + 4 * q < frags) put_w(wave + 4 * q, wpre[q]);
+  for (int f = wave + 4 * kPre; f < frags; f += 4) put_w(f, *w_entry(f));
   for (int o = threadIdx.x; o < nout; o += 256) {
     if constexpr (R2L) {
       const int w = o >> ld2, s = o & (d - 1);
       sOff[o] = (((long)w * p.nq << ld2) + s) * p.na;
     } else {
-      const int s = o / wo, v = o - s * wo;
+      const int s = (int)((o + 0.5f) * rwo), v = o - s * wo;
       sOff[o] = s * p.ld_out + (long)v * p.nq;
     }
   }
@@ -444,40 +454,95 @@ void front_kernel(FParams p) {
   const int npts = am * np, npb = (npts + 15) / 16;
   const int ustep = 4 >> ld2, u0 = g >> ld2, toff = (g & (d - 1)) * (R2L ? 1 : np);
   S* out = reinterpret_cast<S*>(p.out);
-  constexpr int KC = 6;                              // k steps held at a time
-  for (int pb = wave; pb < npb; pb += 4) {
-    const int pt = pb * 16 + lrow;
-    int ia, iq;                                      // the point's A-side and B-side index within the tile
-    if constexpr (R2L) { iq = pt / am; ia = pt - iq * am; }
-    else { ia = pt / np; iq = pt - ia * np; }
-    const bool live = pt < npts && i0 + ia < p.na && q0 + iq < p.nq;
-    if (pt >= npts) { ia = 0; iq = 0; }
-    const S* tb = sT + ia * wx * LDT + (R2L ? iq << ld2 : iq) + toff;
-    S* dst = out + (R2L ? ((long)(q0 + iq) << ld2) * p.na + i0 + ia : ((long)(i0 + ia) << ld2) * p.ld_out + q0 + iq);
+  auto mma = [](S wv, S x, AV& o) {
+    if constexpr (sizeof(S) == 8) o = __builtin_amdgcn_mfma_f64_16x16x4f64(wv, x, o, 0, 0, 0);
+    else o = __builtin_amdgcn_mfma_f32_16x16x4f32(wv, x, o, 0, 0, 0);
+  };
+  const float ram = 1.0f / am;
+  struct Point {
+    const S* tb;                                     // its T1 values
+    S* dst;
+    bool live;
+  };
+  auto point = [&](int pb) {
+    const int pt = pb * 16 + lrow, pc = min(pt, npts - 1);
+    int ia, iq;                                      // A-side and B-side index within the tile
+    if constexpr (R2L) { iq = (int)((pc + 0.5f) * ram); ia = pc - iq * am; }
+    else { ia = pc >> lnp; iq = pc & (np - 1); }
+    return Point{sT + ia * wx * LDT + (R2L ? iq << ld2 : iq) + toff,
+                 out + (R2L ? ((long)(q0 + iq) << ld2) * p.na + i0 + ia : ((long)(i0 + ia) << ld2) * p.ld_out + q0 + iq),
+                 pt < npts && i0 + ia < p.na && q0 + iq < p.nq};
+  };
+  auto store = [&](const Point& pt, const AV& o, const long (&off)[4], int m) {
+    if (pt.live) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (m * 16 + acc_row<S>(r, g) < nout) pt.dst[off[r]] = o[r];
+    }
+  };
+  // Past the last k step a value that is finite for the point meets a zero of
+  // W.  Up to KS steps the W fragments and output offsets of 16 outputs stay in
+  // registers and a wave has two blocks of points in flight: the map of a
+  // small call's tile takes 4500 cycles that way, 6900 with one block after the
+  // other and everything read per block (128 x 120, d = 4, w = 6).
+  auto map = [&](auto kst) {
+    constexpr int KS = decltype(kst)::value;
     for (int m = 0; m < mb; ++m) {
-      AV o = AV{0, 0, 0, 0};
       const S* wf = sW + (long)m * ks * 64 + lane;
-      for (int s0 = 0; s0 < ks; s0 += KC) {
-        S x[KC], wv[KC];
+      S wv[KS];
+      long off[4];
 #pragma unroll
-        for (int s = 0; s < KC; ++s) {
-          // past the end: any finite-for-this-point value against a zero of W
-          const int ss = min(s0 + s, ks - 1);
-          x[s] = tb[min(ss * ustep + u0, wx - 1) * LDT];
-          wv[s] = (s0 + s < ks) ? wf[ss * 64] : S(0);
-        }
+      for (int s = 0; s < KS; ++s) wv[s] = wf[min(s, ks - 1) * 64];
 #pragma unroll
-        for (int s = 0; s < KC; ++s) {
-          if constexpr (sizeof(S) == 8) o = __builtin_amdgcn_mfma_f64_16x16x4f64(wv[s], x[s], o, 0, 0, 0);
-          else o = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[s], x[s], o, 0, 0, 0);
+      for (int r = 0; r < 4; ++r) off[r] = sOff[min(m * 16 + acc_row<S>(r, g), nout - 1)];
+#pragma unroll
+      for (int s = 0; s < KS; ++s) wv[s] = s < ks ? wv[s] : S(0);
+      for (int pb = 2 * wave; pb < npb; pb += 8) {
+        const Point pa = point(pb), pz = point(pb + 1);
+        S x[KS], z[KS];
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+          const int r = min(min(s, ks - 1) * ustep + u0, wx - 1) * LDT;
+          x[s] = pa.tb[r];
+          z[s] = pz.tb[r];
         }
+        AV o = AV{0, 0, 0, 0}, q = AV{0, 0, 0, 0};
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+          mma(wv[s], x[s], o);
+          mma(wv[s], z[s], q);
+        }
+        store(pa, o, off, m);
+        store(pz, q, off, m);
       }
-      if (live) {
+    }
+  };
+  if (ks <= 3) {
+    map(std::integral_constant<int, 3>());
+  } else if (ks <= 6) {
+    map(std::integral_constant<int, 6>());
+  } else {
+    constexpr int KC = 6;                            // k steps held at a time
+    for (int pb = wave; pb < npb; pb += 4) {
+      const Point pa = point(pb);
+      for (int m = 0; m < mb; ++m) {
+        AV o = AV{0, 0, 0, 0};
+        const S* wf = sW + (long)m * ks * 64 + lane;
+        for (int s0 = 0; s0 < ks; s0 += KC) {
+          S x[KC], wv[KC];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int oo = m * 16 + acc_row<S>(r, g);
-          if (oo < nout) dst[sOff[oo]] = o[r];
+          for (int s = 0; s < KC; ++s) {
+            const int ss = min(s0 + s, ks - 1);
+            x[s] = pa.tb[min(ss * ustep + u0, wx - 1) * LDT];
+            wv[s] = (s0 + s < ks) ? wf[ss * 64] : S(0);
+          }
+#pragma unroll
+          for (int s = 0; s < KC; ++s) mma(wv[s], x[s], o);
         }
+        long off[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) off[r] = sOff[min(m * 16 + acc_row<S>(r, g), nout - 1)];
+        store(pa, o, off, m);
       }
     }
   }

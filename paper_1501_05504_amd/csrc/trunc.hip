@@ -141,9 +141,10 @@ void multi_gemm(Ctx* c, const std::vector<MTask>& ts, bool a_kc, bool b_kc, cons
 // with the batch (n = 64, 40 matrices: 18 ms against 2 ms at n = 96).  The
 // library's own solver takes the small ones (one workgroup per matrix, one
 // launch; a batch of up to 256 takes 0.09 ms at n = 32, 0.18 ms at n = 64 and
-// 0.34 ms at n = 96).  Sizes are padded (to a multiple of 8 for the own solver, else to at least 96 and a multiple
-// of 16; a lone matrix is not padded), sorted, and grouped contiguously with
-// the least modelled cost (dynamic programming).
+// 0.34 ms at n = 96).  Sizes are padded (to a multiple of 8 for the own solver,
+// else to at least 96 and a multiple of 16; a lone matrix is not padded),
+// sorted, and grouped contiguously with the least modelled cost (dynamic
+// programming).
 EigPlan plan_eig(Ctx* c, const std::vector<int>& n) {
   EigPlan ep;
   const int Q = (int)n.size();
