@@ -40,7 +40,7 @@ namespace {
 using namespace tile;
 
 constexpr unsigned kOut = 0x80000000u;   // beyond every resource: reads as zero
-constexpr int kFrontRows = 48;           // A-side rows of a front_kernel tile
+constexpr int kFrontRows = 48;           // A-side rows of front_kernel's largest tile
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_at(const void* p) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, 0x7fffffff, 0x00020000);
@@ -548,11 +548,12 @@ void front_kernel(FParams p) {
   }
 }
 
-template <typename S, int TN, bool R2L>
-void front_launch(Ctx* c, const FParams& p, size_t sh) {
+template <typename S, int MT, int TN, bool R2L>
+void front_launch(Ctx* c, FParams p, size_t sh) {
+  p.am = MT * 16 / p.wx;
   const int np = (64 * TN) >> p.ld2;
   const dim3 grid((unsigned)(((p.na + p.am - 1) / p.am) * ((p.nq + np - 1) / np)));
-  hipLaunchKernelGGL((front_kernel<S, kFrontRows / 16, TN, R2L>), grid, dim3(256), sh, c->stream, p);
+  hipLaunchKernelGGL((front_kernel<S, MT, TN, R2L>), grid, dim3(256), sh, c->stream, p);
   D3S_HIP(hipGetLastError());
 }
 
@@ -653,13 +654,31 @@ bool front_dispatch(Ctx* c, bool r2l, FParams p) {
   // 64 columns a tile (one block a wave) until 128 give every compute unit
   // its second workgroup (FP64 m = 128 11.6 against 17.6 us; 512 162 against
   // 138 us)
-  if (tiles2 >= 400) {
-    if (r2l) front_launch<S, 2, true>(c, p, sh);
-    else front_launch<S, 2, false>(c, p, sh);
-  } else {
-    if (r2l) front_launch<S, 1, true>(c, p, sh);
-    else front_launch<S, 1, false>(c, p, sh);
+  // ... and then as many 16-row blocks a tile (3, 2, 1) as give the fewest
+  // block rounds over 256 compute units: a small call spreads over more of
+  // them (FP64, 3 / 2 / 1 blocks, whole product: m = 37 13.3 / 12.6 / 11.7 us,
+  // 128 x 120 22.2 / 20.5 / 21.3, 160 25.5 / 27.2 / 29.3, 192 35.3 / 31.8 /
+  // 36.4, 256 43.8 / 50.0 / 54.7)
+  int mt = 3;
+  long rounds = 1L << 60;
+  for (int m = 3; m >= 1 && m * 16 >= p.wx; --m) {
+    const long r = m * ceil_div(ceil_div(p.na, m * 16 / p.wx) * ceil_div(p.nq, 64 / d), 256);
+    if (r < rounds) {
+      rounds = r;
+      mt = m;
+    }
   }
+  auto go = [&](auto m, auto n) {
+    if (r2l) front_launch<S, decltype(m)::value, decltype(n)::value, true>(c, p, sh);
+    else front_launch<S, decltype(m)::value, decltype(n)::value, false>(c, p, sh);
+  };
+  using I1 = std::integral_constant<int, 1>;
+  using I2 = std::integral_constant<int, 2>;
+  using I3 = std::integral_constant<int, 3>;
+  if (tiles2 >= 400) go(I3(), I2());
+  else if (mt == 1) go(I1(), I1());
+  else if (mt == 2) go(I2(), I1());
+  else go(I3(), I1());
   return true;
 }
 

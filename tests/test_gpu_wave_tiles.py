@@ -152,3 +152,20 @@ def test_lanczos_short_vectors(ctx, ml, d, mr, kmax):
         H = C.heff_matrix(L, W, R)
         ref = np.linalg.eigvalsh((H + H.T) / 2)[0]
         assert abs(th - ref) <= 1e-10 * max(1.0, norm)
+
+
+@pytest.mark.parametrize("ml, d, mr, wl, wr", [(7, 4, 9, 16, 4), (9, 2, 33, 17, 3), (11, 2, 17, 32, 2), (6, 2, 40, 33, 2),
+                                               (96, 4, 96, 6, 6), (130, 2, 128, 8, 8), (129, 4, 121, 6, 5), (193, 4, 192, 6, 6)])
+@pytest.mark.parametrize("dt, tol", [(torch.float64, 1e-12), (torch.float32, 3e-5)])
+def test_fused_front_tile_heights(ctx, ml, d, mr, wl, wr, dt, tol):
+    """MPO bonds that only some of the fused kernel's tile heights (16, 32, 48
+    rows) can hold, and sizes on both sides of the rule that picks among them;
+    both directions through the environment updates."""
+    (L, W, R, psi), (Ld, Wd, Rd, pd) = inputs(ml, d, mr, wl, wr, dt)
+    out = torch.empty(ml, d, mr, dtype=dt, device=DEV)
+    ctx.apply_heff(Ld, Wd, Rd, pd, out)
+    assert rel(out.cpu().numpy(), C.apply_heff(L, W, R, psi)) < tol
+    if dt == torch.float64:
+        env = torch.empty(ml, wl, ml, dtype=dt, device=DEV)
+        ctx.update_env(abi.R2L, Rd, Wd, pd, env)
+        assert rel(env.cpu().numpy(), C.update_right(R, W, psi)) < tol
