@@ -169,3 +169,25 @@ def test_fused_front_tile_heights(ctx, ml, d, mr, wl, wr, dt, tol):
         env = torch.empty(ml, wl, ml, dtype=dt, device=DEV)
         ctx.update_env(abi.R2L, Rd, Wd, pd, env)
         assert rel(env.cpu().numpy(), C.update_right(R, W, psi)) < tol
+
+
+@pytest.mark.parametrize("ml, d, mr, wl, wr", [(1, 2, 4, 3, 2), (2, 2, 2, 2, 2), (3, 2, 8, 4, 4), (33, 4, 64, 2, 3), (64, 3, 66, 5, 4),
+                                               (65, 4, 68, 6, 6), (66, 4, 1028, 8, 3), (130, 1, 63, 3, 3), (31, 4, 124, 9, 2)])
+def test_low_precision_vector_paths(ctx, ml, d, mr, wl, wr):
+    """FP32 and BF16 products whose rows do and do not consist of whole vectors of
+    four (the W-map) or pairs (the transposition of psi).  BF16: T1 is exact
+    to FP32 rounding and T2 is rounded to eight bits, so the error is within
+    2^-9 of the product of absolute values, doubled for the FP32 sums."""
+    (L, W, R, psi), _ = inputs(ml, d, mr, wl, wr, torch.float32)
+    for dt in (torch.float32, torch.bfloat16):
+        Ld, Rd, pd = (torch.tensor(x, device=DEV).to(dt) for x in (L, R, psi))
+        Wd = torch.tensor(W, dtype=torch.float32, device=DEV)
+        out = torch.full((ml, d, mr), float("nan"), dtype=torch.float32, device=DEV)
+        ctx.apply_heff(Ld, Wd, Rd, pd, out)
+        Lh, Rh, ph = (x.double().cpu().numpy() for x in (Ld, Rd, pd))
+        ref, got = C.apply_heff(Lh, W, Rh, ph), out.double().cpu().numpy()
+        if dt == torch.float32:
+            assert rel(got, ref) < 3e-5
+        else:
+            bound = 2.0 ** -8 * C.apply_heff(np.abs(Lh), np.abs(W), np.abs(Rh), np.abs(ph))
+            assert np.all(np.abs(got - ref) <= bound)
