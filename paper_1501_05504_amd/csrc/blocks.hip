@@ -948,7 +948,7 @@ static bool uses_psit(const BlockHeff& h, d3s_prec p) { return p != D3S_F64 && h
 
 static void enqueue_block_heff(Ctx* c, hipStream_t s, const BlockHeff& h, d3s_prec p, const void* L, const void* W,
                                const void* R, const void* psi, void* out, void* T1, void* T2, void* part,
-                               void* psiT) {
+                               void* psiT) {     // out null: the partial products stay in part
   hipStream_t keep = c->stream;
   c->stream = s;
   const size_t osz = (p == D3S_F64) ? 8 : 4;
@@ -965,7 +965,7 @@ static void enqueue_block_heff(Ctx* c, hipStream_t s, const BlockHeff& h, d3s_pr
   if (!h.packed) zero_bytes(c, out, osz * (size_t)h.ml * h.d * h.mr);
   if (h.g2_split > 1) {
     grouped_gemm(c, p, h.g2, T2, R, part, 1.0);
-    sum_partials(c, p == D3S_F64, part, h.g2_split, h.npacked, out);
+    if (out) sum_partials(c, p == D3S_F64, part, h.g2_split, h.npacked, out);
   } else {
     grouped_gemm(c, p, h.g2, T2, R, out, 1.0);
   }
@@ -973,7 +973,7 @@ static void enqueue_block_heff(Ctx* c, hipStream_t s, const BlockHeff& h, d3s_pr
 }
 
 void op_apply_heff_blocks(Ctx* c, BlockHeff& h, d3s_prec p, const void* L, const void* W, const void* R,
-                          const void* psi, void* out, bool use_graph) {
+                          const void* psi, void* out, bool use_graph, const float** partials) {
   if (p != D3S_F64 && !h.padded) {
     // operands of the plan's layouts, in the product's element type: moved
     // into the padded twin's layouts, multiplied there, the product moved back
@@ -998,6 +998,10 @@ void op_apply_heff_blocks(Ctx* c, BlockHeff& h, d3s_prec p, const void* L, const
   void* T2 = ws_get(c, WS_T2, t2sz * (size_t)h.ml * h.d * h.wr * h.mr);
   void* part = (h.g2_split > 1) ? ws_get(c, WS_G2_PART, tsz * (size_t)h.g2_split * h.npacked) : nullptr;
   void* psiT = uses_psit(h, p) ? ws_get(c, WS_PSIT, t2sz * (size_t)h.npacked) : nullptr;
+  if (partials && part && h.packed && p != D3S_F64) {
+    *partials = (const float*)part;
+    out = nullptr;
+  }
   if (!use_graph) {
     enqueue_block_heff(c, c->stream, h, p, L, W, R, psi, out, T1, T2, part, psiT);
     return;
@@ -1051,10 +1055,12 @@ void op_apply_heff_blocks(Ctx* c, BlockHeff& h, d3s_prec p, const void* L, const
 void lowp_product(Ctx* c, BlockHeff& h, LowpTwin& tw, d3s_prec p, const void* Lc, const void* Wc, const void* Rc,
                   const double* x, double* y, void* xin, float* yout, bool use_graph) {
   relayout_tiles(c, RL_F64, p == D3S_F32 ? RL_F32 : RL_BF16, x, xin, tw.d_X, tw.nX);
-  op_apply_heff_blocks(c, tw.h, p, Lc, Wc, Rc, xin, yout, use_graph);
+  const float* part = nullptr;
+  op_apply_heff_blocks(c, tw.h, p, Lc, Wc, Rc, xin, yout, use_graph, &part);
   // the dense layout's forbidden entries are not written by the relayout
   if (!h.packed) zero_bytes(c, y, sizeof(double) * (size_t)h.ml * h.d * h.mr);
-  relayout_tiles(c, RL_F32, RL_F64, yout, y, tw.d_Y, tw.nY);
+  if (part) relayout_sum(c, part, tw.h.g2_split, tw.h.npacked, y, tw.d_Y, tw.nY);
+  else relayout_tiles(c, RL_F32, RL_F64, yout, y, tw.d_Y, tw.nY);
 }
 
 void op_block_bind(Ctx* c, BlockHeff& h, d3s_prec p, const double* L, const double* W, const double* R) {

@@ -413,6 +413,8 @@ EnvPack build_envpack(const Sectors& s, const int* wq, int w);
 struct RlTile { long src, dst; int src_ld, dst_ld, rows, cols, prows, pcols; };
 enum { RL_F64 = 0, RL_F32 = 1, RL_BF16 = 2 };
 void relayout_tiles(Ctx* c, int in_kind, int out_kind, const void* in, void* out, const RlTile* tiles, int ntiles);
+// the FP32 sum of `parts` partial products of n elements, to FP64 in the tiles' layout
+void relayout_sum(Ctx* c, const float* part, int parts, long n, double* out, const RlTile* tiles, int ntiles);
 struct LowpTwin;
 
 // One tile (at most 32 x 32) of a batched block transpose:
@@ -507,7 +509,8 @@ void lowp_product(Ctx* c, BlockHeff& h, LowpTwin& tw, d3s_prec p, const void* Lc
 void op_block_bind(Ctx* c, BlockHeff& h, d3s_prec p, const double* L, const double* W, const double* R);
 void op_apply_heff_blocks_bound(Ctx* c, BlockHeff& h, const double* psi, double* out, bool use_graph);
 void op_apply_heff_blocks(Ctx* c, BlockHeff& h, d3s_prec p, const void* L, const void* W, const void* R,
-                          const void* psi, void* out, bool use_graph);
+                          const void* psi, void* out, bool use_graph,
+                          const float** partials = nullptr);
 // Block-sparse expansion (FP64): writes the allowed blocks of Mt = [psi | P]
 // (L2R, env = L, row length (1+wr)*mr) or [psi ; P] (R2L, env = R, row length
 // d*mr) and zeroes the rest.
