@@ -572,6 +572,11 @@ bool direct_dispatch(Ctx* c, const GemmArgs& g) {
   if (t32 > (1L << 30)) return false;
   const int steps = g.K / BK;
   // Who shares a tile's K (measured on MI355X, FP64 and FP32):
+  //  - too few 32x32 tiles for half of the chip: 16x16 tiles, a K loop a
+  //    quarter as long, by four or (long sums) eight waves (FP64 384 x 96 x 576
+  //    5.3 us, 32x32 tiles 9.6; 512 x 120 x 720 5.4 against 10.7; 640 x 160 x
+  //    960 8.7 against 12.3; 768 x 192 x 1152 12.4 against 14.4; 1024 x 250 x
+  //    1500 26.2 against 20.2, where operands come twice as often from L2);
   //  - fewer 32x32 tiles than compute units: eight waves a tile while each
   //    gets two K steps or more, else four; very long sums are split over the
   //    grid too, which costs a summing launch (about 5 us);
@@ -613,7 +618,10 @@ bool direct_dispatch(Ctx* c, const GemmArgs& g) {
   using I2 = std::integral_constant<int, 2>;
   using I4 = std::integral_constant<int, 4>;
   using I8 = std::integral_constant<int, 8>;
-  if (t32 <= 320) {
+  if (t32 <= 160 && splits == 1) {
+    if (steps >= 40) go(I1(), I1(), I8(), I2());
+    else go(I1(), I1(), I4(), I2());
+  } else if (t32 <= 320) {
     if (steps >= 16) go(I2(), I2(), I8(), I2());
     else go(I2(), I2(), I4(), I2());
   } else if (t32 >= 900 && t32 < 4096 && steps >= 64) {

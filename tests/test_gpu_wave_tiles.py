@@ -191,3 +191,16 @@ def test_low_precision_vector_paths(ctx, ml, d, mr, wl, wr):
         else:
             bound = 2.0 ** -8 * C.apply_heff(np.abs(Lh), np.abs(W), np.abs(Rh), np.abs(ph))
             assert np.all(np.abs(got - ref) <= bound)
+
+
+@pytest.mark.parametrize("ml, d, mr, w", [(1, 1, 1, 1), (15, 1, 17, 2), (16, 1, 16, 3), (17, 3, 15, 2), (33, 3, 16, 5), (31, 1, 47, 7),
+                                          (48, 3, 49, 5), (64, 3, 120, 9), (129, 3, 96, 6), (150, 3, 160, 6)])
+@pytest.mark.parametrize("dt, tol", [(torch.float64, 1e-12), (torch.float32, 3e-5)])
+def test_small_wave_tiles(ctx, ml, d, mr, w, dt, tol):
+    """Products of few tiles, on both sides of a 16-row tile, of the wave count's
+    rule (40 K steps) and of the tile count at which larger tiles take over; a
+    physical dimension that the fused kernel does not take."""
+    (L, W, R, psi), (Ld, Wd, Rd, pd) = inputs(ml, d, mr, w, w, dt)
+    out = torch.empty(ml, d, mr, dtype=dt, device=DEV)
+    ctx.apply_heff(Ld, Wd, Rd, pd, out)
+    assert rel(out.cpu().numpy(), C.apply_heff(L, W, R, psi)) < tol
