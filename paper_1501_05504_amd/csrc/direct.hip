@@ -480,8 +480,12 @@ void front_kernel(FParams p) {
         if (m * 16 + acc_row<S>(r, g) < nout) pt.dst[off[r]] = o[r];
     }
   };
-  // Past the last k step a value that is finite for the point meets a zero of
-  // W.  Up to KS steps the W fragments and output offsets of 16 outputs stay in
+  // Steps past the last k are skipped, and the lane groups past it in a step (d =
+  // 2 and odd w) have zeros of T1 beside those of W: an infinite T1 value makes
+  // its outputs infinite, not NaN.
+  const bool part = (kin & 3) != 0;
+  auto past = [&](int s) { return 4 * s + g >= kin; };
+  // Up to KS steps the W fragments and output offsets of 16 outputs stay in
   // registers and a wave has two blocks of points in flight: the map of a
   // small call's tile takes 4500 cycles that way, 6900 with one block after the
   // other and everything read per block (128 x 120, d = 4, w = 6).
@@ -506,12 +510,20 @@ void front_kernel(FParams p) {
           x[s] = pa.tb[r];
           z[s] = pz.tb[r];
         }
+        if (part) {
+#pragma unroll
+          for (int s = 0; s < KS; ++s) {
+            x[s] = past(s) ? S(0) : x[s];
+            z[s] = past(s) ? S(0) : z[s];
+          }
+        }
         AV o = AV{0, 0, 0, 0}, q = AV{0, 0, 0, 0};
 #pragma unroll
-        for (int s = 0; s < KS; ++s) {
-          mma(wv[s], x[s], o);
-          mma(wv[s], z[s], q);
-        }
+        for (int s = 0; s < KS; ++s)
+          if (s < ks) {
+            mma(wv[s], x[s], o);
+            mma(wv[s], z[s], q);
+          }
         store(pa, o, off, m);
         store(pz, q, off, m);
       }
@@ -536,8 +548,13 @@ void front_kernel(FParams p) {
             x[s] = pa.tb[min(ss * ustep + u0, wx - 1) * LDT];
             wv[s] = (s0 + s < ks) ? wf[ss * 64] : S(0);
           }
+          if (part) {
 #pragma unroll
-          for (int s = 0; s < KC; ++s) mma(wv[s], x[s], o);
+            for (int s = 0; s < KC; ++s) x[s] = past(s0 + s) ? S(0) : x[s];
+          }
+#pragma unroll
+          for (int s = 0; s < KC; ++s)
+            if (s0 + s < ks) mma(wv[s], x[s], o);
         }
         long off[4];
 #pragma unroll

@@ -204,3 +204,34 @@ def test_small_wave_tiles(ctx, ml, d, mr, w, dt, tol):
     out = torch.empty(ml, d, mr, dtype=dt, device=DEV)
     ctx.apply_heff(Ld, Wd, Rd, pd, out)
     assert rel(out.cpu().numpy(), C.apply_heff(L, W, R, psi)) < tol
+
+
+@pytest.mark.parametrize("d, w", [(2, 1), (2, 3), (2, 5), (2, 7), (2, 13), (4, 1), (4, 2), (4, 4), (4, 5), (4, 6), (4, 9)])
+@pytest.mark.parametrize("dt", [torch.float64, torch.float32], ids=["f64", "f32"])
+def test_infinite_entry_gives_infinite_outputs(ctx, d, w, dt):
+    """With positive operands an Inf in one row of L makes every output of that
+    row +Inf, not NaN, whatever the sum over the MPO bond is padded to (both
+    counts of its steps that stay in registers, and more); the other rows agree
+    with the oracle.  FP64: the expansion term in both directions as well."""
+    ml, mr, a = 21, 18, 5
+    g = [np.abs(x) for x in inputs(ml, d, mr, w, w, dt)[0]]
+    ref = C.apply_heff(*g)
+    t = [torch.tensor(x, dtype=dt, device=DEV) for x in g]
+    t[0][a, w - 1, 7] = float("inf")
+    out = torch.empty((ml, d, mr), dtype=dt, device=DEV)
+    ctx.apply_heff(*t, out)
+    o = out.cpu().double().numpy()
+    keep = np.arange(ml) != a
+    assert np.all(o[a] == np.inf)
+    assert rel(o[keep], ref[keep]) < (1e-12 if dt == torch.float64 else 3e-5)
+    if dt == torch.float64:
+        M = torch.empty((ml * d, (1 + w) * mr), dtype=dt, device=DEV)
+        ctx.expand_subspace(abi.L2R, t[0], t[1], t[3], 0.5, M)
+        o = M.cpu().numpy()[:, mr:].reshape(ml, d, w, mr)
+        assert np.all(o[a] == np.inf) and np.isfinite(o[keep]).all()
+        t[2][3, w - 1, 7] = float("inf")
+        M = torch.empty(((1 + w) * ml, d * mr), dtype=dt, device=DEV)
+        ctx.expand_subspace(abi.R2L, t[2], t[1], t[3], 0.5, M)
+        o = M.cpu().numpy()[ml:].reshape(w, ml, d, mr)
+        keep = np.arange(mr) != 3
+        assert np.all(o[..., 3] == np.inf) and np.isfinite(o[..., keep]).all()
