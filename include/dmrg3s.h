@@ -183,11 +183,14 @@ d3s_status d3s_apply_heff_noalloc(d3s_ctx ctx, d3s_prec prec, int ml, int d, int
                                   const void* L, const void* W, const void* R, const void* psi, void* out);
 
 /* Per-kernel timing of d3s_apply_heff: while enabled, HIP events are
- * recorded on the context's stream around each of its three launches (GEMM
+ * recorded on the context's stream around each of its three steps (GEMM
  * over the left bond, W-map, GEMM over (v, y)) for up to `capacity` calls.
  * d3s_profile_end synchronises, writes the summed milliseconds of the three
- * kernels to total_ms[0..2] (host) and the number of timed calls to *count,
- * and disables the recording. */
+ * steps to total_ms[0..2] (host) and the number of timed calls to *count,
+ * and disables the recording.  Where the first two steps run as one launch
+ * (FP64 and FP32, small and medium products; never with a tile configuration
+ * chosen by d3s_set_tile_config), its time is in total_ms[0] and the call adds
+ * nothing, exactly, to total_ms[1]. */
 d3s_status d3s_profile_begin(d3s_ctx ctx, int capacity);
 d3s_status d3s_profile_end(d3s_ctx ctx, double* total_ms, int* count);
 

@@ -328,7 +328,9 @@ class Context:
         self._check(_profile_begin(self.h, capacity))
 
     def profile_end(self):
-        """Returns ([ms GEMM-1, ms W-map, ms GEMM-2] summed, number of calls)."""
+        """Returns ([ms GEMM-1, ms W-map, ms GEMM-2] summed, number of calls); a
+        call whose GEMM-1 and W-map are one launch counts it as GEMM-1 and adds
+        0 to the W-map."""
         ms = (ctypes.c_double * 3)()
         n = c_int()
         self._check(_profile_end(self.h, ms, ctypes.byref(n)))

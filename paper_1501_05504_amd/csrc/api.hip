@@ -245,6 +245,7 @@ d3s_status d3s_profile_begin(d3s_ctx ctx, int capacity) {
       D3S_HIP(hipEventCreate(&e));
       ctx->c.prof_ev.push_back(e);
     }
+    ctx->c.prof_fused.resize(ctx->c.prof_ev.size() / 4);
     ctx->c.prof_cap = capacity;
     ctx->c.prof_n = 0;
     ctx->c.prof = true;
@@ -259,6 +260,7 @@ d3s_status d3s_profile_end(d3s_ctx ctx, double* total_ms, int* count) {
     total_ms[0] = total_ms[1] = total_ms[2] = 0.0;
     for (int i = 0; i < ctx->c.prof_n; ++i) {
       for (int k = 0; k < 3; ++k) {
+        if (k == 1 && ctx->c.prof_fused[i]) continue;    // no launch between these events
         float ms = 0.f;
         D3S_HIP(hipEventElapsedTime(&ms, ctx->c.prof_ev[4 * i + k], ctx->c.prof_ev[4 * i + k + 1]));
         total_ms[k] += ms;

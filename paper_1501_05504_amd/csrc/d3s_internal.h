@@ -84,6 +84,7 @@ struct Ctx {
   bool prof = false;
   int prof_cap = 0, prof_n = 0;
   std::vector<hipEvent_t> prof_ev;   // 4 per recorded application
+  std::vector<char> prof_fused;      // per application: GEMM-1 and W-map were one launch
 };
 
 void* ws_get(Ctx* c, int slot, size_t bytes);

@@ -109,11 +109,19 @@ void heff_product(Ctx* c, d3s_prec p, int ml, int d, int mr, int wl, int wr, con
                   const void* R, const void* psi, void* out, void* T1, void* T2, void* psiT, void* part,
                   size_t part_cap, bool plain) {
   hipEvent_t* ev = nullptr;
-  if (!plain && c->prof && c->prof_n < c->prof_cap) ev = &c->prof_ev[4 * (size_t)c->prof_n++];
+  char* fused = nullptr;
+  if (!plain && c->prof && c->prof_n < c->prof_cap) {
+    fused = &c->prof_fused[c->prof_n];
+    ev = &c->prof_ev[4 * (size_t)c->prof_n++];
+    *fused = 0;
+  }
   if (ev) D3S_HIP(hipEventRecord(ev[0], c->stream));
   if (front_wmap(c, p, D3S_L2R, ml, d, mr, wl, wr, L, W, psi, T2, (long)wr * mr, 1.0)) {
     // GEMM-1 and the W-map in one launch: timed as GEMM-1
-    if (ev) D3S_HIP(hipEventRecord(ev[1], c->stream));
+    if (ev) {
+      *fused = 1;
+      D3S_HIP(hipEventRecord(ev[1], c->stream));
+    }
   } else {
     // GEMM-1's B operand psi[x][(t,y)] runs along N; a copy psi^T[(t,y)][x]
     // runs along K, which keeps the LDS staging of B in 16-byte vector stores

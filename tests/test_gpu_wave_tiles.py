@@ -235,3 +235,33 @@ def test_infinite_entry_gives_infinite_outputs(ctx, d, w, dt):
         o = M.cpu().numpy()[ml:].reshape(w, ml, d, mr)
         keep = np.arange(mr) != 3
         assert np.all(o[..., 3] == np.inf) and np.isfinite(o[..., keep]).all()
+
+
+def step_times(ctx, shape, dt, calls=4):
+    """Summed milliseconds of GEMM-1, W-map and GEMM-2 over `calls` products."""
+    ml, d, mr, wl, wr = shape
+    t = [torch.randn(s, dtype=dt, device=DEV) for s in [(ml, wl, ml), (wl, wr, d, d), (mr, wr, mr), (ml, d, mr)]]
+    out = torch.empty((ml, d, mr), dtype=dt, device=DEV)
+    ctx.apply_heff(*t, out)
+    ctx.profile_begin(calls)
+    for _ in range(calls):
+        ctx.apply_heff(*t, out)
+    ms, n = ctx.profile_end()
+    assert n == calls
+    return ms
+
+
+@pytest.mark.parametrize("dt", [torch.float64, torch.float32], ids=["f64", "f32"])
+def test_profile_of_fused_steps(ctx, dt):
+    """The profile has no time at all for a W-map that was part of GEMM-1's
+    launch, and a time for one that ran by itself."""
+    small = (37, 4, 29, 6, 6)
+    ms = step_times(ctx, small, dt)
+    assert ms[0] > 0 and ms[1] == 0 and ms[2] > 0
+    ctx.set_tile_config(1)
+    try:
+        ms = step_times(ctx, small, dt)
+    finally:
+        ctx.set_tile_config(-1)
+    assert min(ms) > 0
+    assert step_times(ctx, small, dt)[1] == 0
