@@ -133,8 +133,9 @@ bool gemm_direct(Ctx* c, d3s_prec p, const GemmArgs& g);
 // out[(a,s)*ld_out + v*mr + y]) or right-to-left contraction (Y = psi env^T
 // over the right bond; out[w, x, s, b]) in one launch, scaled by alpha; false
 // (nothing launched) where the separate kernels are faster or d, w do not fit.
+// copied: the separate kernels would work on a K-contiguous copy of psi.
 bool front_wmap(Ctx* c, d3s_prec p, d3s_dir dir, int ml, int d, int mr, int wl, int wr, const void* env,
-                const void* W, const void* psi, void* out, long ld_out, double alpha);
+                const void* W, const void* psi, void* out, long ld_out, double alpha, bool copied = false);
 
 // ---------------------------------------------------------------- grouped GEMM
 // One output block per task, sum over the task's K-segments (see grouped.hip).

@@ -655,7 +655,7 @@ bool direct_dispatch(Ctx* c, const GemmArgs& g) {
 }
 
 template <typename S>
-bool front_dispatch(Ctx* c, bool r2l, FParams p) {
+bool front_dispatch(Ctx* c, bool r2l, bool copied, FParams p) {
   constexpr bool f64 = sizeof(S) == 8;
   const int d = 1 << p.ld2;
   p.am = kFrontRows / p.wx;
@@ -665,17 +665,24 @@ bool front_dispatch(Ctx* c, bool r2l, FParams p) {
   auto ceil_div = [](long a, long b) { return (a + b - 1) / b; };
   const long ta = ceil_div(p.na, p.am), tiles2 = ta * ceil_div(p.nq, 128 / d), tiles1 = ta * ceil_div(p.nq, 64 / d);
   if (tiles1 > (1L << 30)) return false;
-  // Against the three launches it replaces (a transposed copy of psi, the
-  // GEMM, the W-map): the K loop reaches 64 (FP64) and 121 (FP32) TFLOP/s on
-  // whole tiles, below the workgroup-tiled GEMM's best, but T1 costs those a
-  // write and a read of memory.  FP64, d = 4, w = 6, this kernel against the
-  // three: m = 37 8.7 against 21 us, 256 27 against 43 us, 512 138 against
-  // 214 us, 1024 840 against 805 us, 2048 6.41 against 5.90 ms.
-  const double t_front = 2.0 * tiles2 * kFrontRows * 128.0 * p.K / (f64 ? 64e12 : 121e12);
+  // Against the launches it replaces (for H_eff a transposed copy of psi, the
+  // GEMM, the W-map): over m = 300 ... 2400 the kernel reaches 50 to 63 (FP64)
+  // and 85 to 118 (FP32) TFLOP/s of its whole tiles, 60 and 102 in the middle of
+  // the sizes where the two are close, below the workgroup-tiled GEMM's best;
+  // but T1 costs the others a write and a read of memory, at 5 TB/s, and the
+  // launches and their gaps 20 us.  Expansion and environments have no copy of
+  // psi, a GEMM on its own layout and a W-map into other rows: 7 % more for the
+  // GEMM, 3.3 TB/s, 10 us (m = 1024 right to left 801 / 831 us, 1200 left to
+  // right 1423 / 1483, 1800 4825 / 4625).  H_eff, d = 4,
+  // w = 6, this kernel against the launches, FP64: m = 300 51 / 68 us, 512
+  // 125 / 141, 800 433 / 444, 900 646 / 642, 1024 835 / 795, 1200 1452 / 1403, 1400
+  // 2466 / 2113, 1600 3211 / 3040; FP32: 300 35 / 49, 600 122 / 142, 800 236 /
+  // 230, 1024 458 / 427, 1400 1235 / 1117.
+  const double t_front = 2.0 * tiles2 * kFrontRows * 128.0 * p.K / (f64 ? 60e12 : 102e12);
   const double rows = (double)p.na * p.wx, cols = (double)p.nq * d;
   const double t_gemm = gemm_estimate(f64 ? D3S_F64 : D3S_F32, (int)rows, (int)cols, p.K).seconds;
-  const double t_map = (double)sizeof(S) * (rows * cols + (double)p.na * p.nq * nout) / 3.5e12;
-  if (t_front > t_gemm + t_map + 10e-6) return false;
+  const double bytes = (double)sizeof(S) * (rows * cols + (double)p.na * p.nq * nout);
+  if (t_front > (copied ? t_gemm + bytes / 5e12 + 20e-6 : 1.067 * t_gemm + bytes / 3.3e12 + 10e-6)) return false;
   // 64 columns a tile (one block a wave) until 128 give every compute unit
   // its second workgroup (FP64 m = 128 11.6 against 17.6 us; 512 162 against
   // 138 us)
@@ -743,7 +750,7 @@ bool gemm_direct(Ctx* c, d3s_prec p, const GemmArgs& g) {
 }
 
 bool front_wmap(Ctx* c, d3s_prec p, d3s_dir dir, int ml, int d, int mr, int wl, int wr, const void* env,
-                const void* W, const void* psi, void* out, long ld_out, double alpha) {
+                const void* W, const void* psi, void* out, long ld_out, double alpha, bool copied) {
   // a chosen or tuned tile configuration means the separate kernels
   if (p == D3S_BF16 || (d != 2 && d != 4) || c->tile_config >= 0 || c->autotune) return false;
   const bool r2l = dir == D3S_R2L;
@@ -764,7 +771,7 @@ bool front_wmap(Ctx* c, d3s_prec p, d3s_dir dir, int ml, int d, int mr, int wl, 
   const long ldb = r2l ? mr : (long)d * mr;
   if (f.wx > kFrontRows || f.lda > kMaxLd || ldb > kMaxLd) return false;
   f.ldb = (int)ldb;
-  return p == D3S_F64 ? front_dispatch<double>(c, r2l, f) : front_dispatch<float>(c, r2l, f);
+  return p == D3S_F64 ? front_dispatch<double>(c, r2l, copied, f) : front_dispatch<float>(c, r2l, copied, f);
 }
 
 }  // namespace d3s

@@ -116,7 +116,7 @@ void heff_product(Ctx* c, d3s_prec p, int ml, int d, int mr, int wl, int wr, con
     *fused = 0;
   }
   if (ev) D3S_HIP(hipEventRecord(ev[0], c->stream));
-  if (front_wmap(c, p, D3S_L2R, ml, d, mr, wl, wr, L, W, psi, T2, (long)wr * mr, 1.0)) {
+  if (front_wmap(c, p, D3S_L2R, ml, d, mr, wl, wr, L, W, psi, T2, (long)wr * mr, 1.0, true)) {
     // GEMM-1 and the W-map in one launch: timed as GEMM-1
     if (ev) {
       *fused = 1;
