@@ -329,12 +329,18 @@ namespace {
 
 // FP64 and FP32 without a chosen tile configuration: wave tiles while the
 // product has fewer than 4096 tiles of 32x32 (four a SIMD), the least
-// modelled time above
+// modelled time above.  Long sums change over earlier, at 3600 tiles from 64 K
+// steps of 128 bytes on and at 1950 from 512 on: their 64x32 wave tiles then read
+// more operand rows from L2 than the last round of split workgroup tiles wastes.
+// FP64, wave tiles against the model's choice: 2000 x 1939 x 11634 (3843 tiles)
+// 2121 / 1334 us, 2000 x 2040 x 4080 (4032) 599 / 473, 1000 x 1939 x 11634 (1952)
+// 853 / 740; below, 1924 x 1300 x 7800 (2501) 661 against 698 modelled.
 template <typename S>
 void gemm_auto(Ctx* c, d3s_prec p, const GemmArgs& g) {
   if (c->tile_config < 0) {
     const double t32 = std::ceil(g.M / 32.0) * std::ceil(g.N / 32.0) * g.batch;
-    if (t32 < 4096 || g.batch > 1) {
+    const int steps = g.K / (128 / (int)sizeof(S));
+    if (t32 < (steps >= 512 ? 1950 : steps >= 64 ? 3600 : 4096) || g.batch > 1) {
       if (gemm_direct(c, p, g)) return;
     } else {
       const GemmChoice ch = gemm_estimate(p, g.M, g.N, g.K);

@@ -275,3 +275,27 @@ def test_fused_steps_where_they_are_faster(ctx, shape, fused, dt):
     """GEMM-1 and the W-map are one launch at the sizes where that is measured
     to be 13 to 50 % faster, and two where it is 5 to 17 % slower."""
     assert (step_times(ctx, shape, dt)[1] == 0) == fused
+
+
+@pytest.mark.parametrize("dt", [torch.float64, torch.float32], ids=["f64", "f32"])
+@pytest.mark.parametrize("ml, mr", [(250, 1939), (500, 1939)])
+def test_long_sums_of_many_tiles(ctx, ml, mr, dt):
+    """The last GEMM of H_eff at 1952 and 3843 tiles of 32x32 with a sum over
+    11634 elements takes no longer by the rule than on 256x128 workgroup tiles
+    (FP64: it was 3 and 31 % more), ten per cent allowed for two timings; split
+    sums agree with the oracle."""
+    shape = (ml, 4, mr, 6, 6)
+    best = lambda: min(step_times(ctx, shape, dt)[2] for _ in range(4))
+    ctx.set_tile_config(2)
+    try:
+        fixed = best()
+    finally:
+        ctx.set_tile_config(-1)
+    assert best() <= 1.1 * fixed
+    g = [synth.gaussian(s, 970 + i) for i, s in enumerate([(ml, 6, ml), (6, 6, 4, 4), (mr, 6, mr), (ml, 4, mr)])]
+    t = [torch.tensor(x, dtype=dt, device=DEV) for x in g]
+    out = torch.full((ml, 4, mr), float("nan"), dtype=dt, device=DEV)
+    ctx.apply_heff(*t, out)
+    L, W, R, psi = [x.double().cpu().numpy() for x in t]
+    ref = C.apply_heff(L, W, R, psi)
+    assert rel(out.cpu().double().numpy(), ref) < (1e-12 if dt == torch.float64 else 3e-5)
