@@ -240,8 +240,9 @@ def test_infinite_entry_gives_infinite_outputs(ctx, d, w, dt):
 def step_times(ctx, shape, dt, calls=4):
     """Summed milliseconds of GEMM-1, W-map and GEMM-2 over `calls` products."""
     ml, d, mr, wl, wr = shape
-    t = [torch.randn(s, dtype=dt, device=DEV) for s in [(ml, wl, ml), (wl, wr, d, d), (mr, wr, mr), (ml, d, mr)]]
-    out = torch.empty((ml, d, mr), dtype=dt, device=DEV)
+    wide = torch.float32 if dt == torch.bfloat16 else dt
+    t = [torch.randn(s, device=DEV).to(e) for s, e in [((ml, wl, ml), dt), ((wl, wr, d, d), wide), ((mr, wr, mr), dt), ((ml, d, mr), dt)]]
+    out = torch.empty((ml, d, mr), dtype=wide, device=DEV)
     ctx.apply_heff(*t, out)
     ctx.profile_begin(calls)
     for _ in range(calls):
@@ -299,3 +300,43 @@ def test_long_sums_of_many_tiles(ctx, ml, mr, dt):
     L, W, R, psi = [x.double().cpu().numpy() for x in t]
     ref = C.apply_heff(L, W, R, psi)
     assert rel(out.cpu().double().numpy(), ref) < (1e-12 if dt == torch.float64 else 3e-5)
+
+
+@pytest.mark.parametrize("m, w", [(32, 8), (64, 8), (128, 8), (128, 6)])
+def test_small_map_of_whole_vectors(ctx, m, w):
+    """BF16: at small bonds the W-map takes no longer for rows of whole vectors
+    than for the next shorter, ragged ones (it was 1.6 to 1.8 times as long);
+    a quarter more allowed for two timings."""
+    best = lambda mr: min(step_times(ctx, (m, 4, mr, w, w), torch.bfloat16, 20)[1] for _ in range(5))
+    ragged = best(m - 1)
+    assert best(m) <= 1.25 * ragged
+
+
+@pytest.mark.parametrize("ml, mr", [(1876, 192), (1876, 188), (580, 600), (510, 600), (330, 1096), (330, 1100), (240, 1548),
+                                    (240, 1552), (340, 1496), (401, 1500), (200, 1696), (200, 1700)])
+@pytest.mark.parametrize("w", [6, 8])
+def test_map_rule_edges(ctx, ml, mr, w):
+    """FP32 and BF16 products on both sides of the sizes at which the W-map
+    changes between one and four columns a thread; bounds as in
+    test_low_precision_vector_paths."""
+    d, rng = 4, np.random.default_rng(ml + mr)
+    L, W, R, psi = [torch.tensor(rng.standard_normal(s), device=DEV) for s in [(ml, w, ml), (w, w, d, d), (mr, w, mr), (ml, d, mr)]]
+    for dt in (torch.float32, torch.bfloat16):
+        a = [L.to(dt), W.float(), R.to(dt), psi.to(dt)]
+        out = torch.full((ml, d, mr), float("nan"), dtype=torch.float32, device=DEV)
+        ctx.set_tile_config(1)             # the W-map by itself in FP32 too
+        try:
+            ctx.apply_heff(*a, out)
+        finally:
+            ctx.set_tile_config(-1)
+
+        def ref(f):                        # the oracle's contraction order, on the device
+            l, x, r, p = (f(v.double()) for v in a)
+            T = torch.matmul(l.reshape(ml * w, ml), p.reshape(ml, d * mr)).reshape(ml, w, d, mr)
+            T = torch.tensordot(T, x, dims=([1, 2], [0, 3])).permute(0, 3, 2, 1).reshape(ml * d, w * mr).contiguous()
+            return torch.matmul(T, r.reshape(mr, w * mr).t().contiguous()).reshape(ml, d, mr)
+        err = (out.double() - ref(lambda v: v)).abs()
+        if dt == torch.float32:
+            assert float(err.max() / ref(lambda v: v).abs().max()) < 3e-5
+        else:
+            assert bool((err <= 2.0 ** -8 * ref(torch.abs)).all())
