@@ -100,10 +100,13 @@ d3s_status d3s_set_grouped_tile(d3s_ctx ctx, int cfg);
 d3s_status d3s_set_block_split(d3s_ctx ctx, double min_gflop);
 /* Autotuning of tile configurations (default off: a size heuristic picks
  * them).  When on, the first dense GEMM of every shape class (precision,
- * layouts, M, N, K) is timed in all tile configurations with HIP events and
- * the fastest is kept, and block plans time both tile sizes of their grouped
- * launches when they are created.  cache_path (may be NULL) names a text file
- * of "key config" lines read now and appended to on every new decision.
+ * layouts, M, N, K) is timed in all tile configurations and as the heuristic
+ * would run it, with HIP events, and the fastest is kept; H_eff's first GEMM
+ * and W-map are timed as one launch too where the heuristic would fuse them.
+ * Block plans time all tile sizes of their grouped launches when they are
+ * created.  cache_path (may be NULL) names a text file of "key:how config"
+ * lines (how = tile, rule or fused) read now and appended to on every new
+ * decision; lines without a known `how` are passed over.
  * Tuning never happens during graph capture or for accumulating products. */
 d3s_status d3s_set_autotune(d3s_ctx ctx, int enable, const char* cache_path);
 /* Batched eigensolver of the per-sector Gram matrices in the block-sparse

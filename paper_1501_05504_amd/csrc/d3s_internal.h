@@ -170,6 +170,11 @@ void grouped_retile(Ctx* c, GroupedPlan& g);
 // autotuner (autotune.hip)
 void autotune_load(Ctx* c);
 void tuned_gemm(Ctx* c, d3s_prec p, const GemmArgs& g);
+// GEMM-1 and the W-map of H_eff with the autotuner on: fused() (one launch;
+// false: not run) or separate(gemm1), which calls gemm1 between its other
+// launches.  True: fused.
+bool tuned_first(Ctx* c, d3s_prec p, const GemmArgs& g1, int d, const std::function<bool()>& fused,
+                 const std::function<void(const std::function<void()>&)>& separate);
 void tune_grouped(Ctx* c, GroupedPlan& g, const void* A, const void* B, void* C);
 void grouped_release(GroupedPlan& g);
 void grouped_gemm(Ctx* c, d3s_prec p, const GroupedPlan& g, const void* A, const void* B, void* C,

@@ -751,8 +751,8 @@ bool gemm_direct(Ctx* c, d3s_prec p, const GemmArgs& g) {
 
 bool front_wmap(Ctx* c, d3s_prec p, d3s_dir dir, int ml, int d, int mr, int wl, int wr, const void* env,
                 const void* W, const void* psi, void* out, long ld_out, double alpha, bool copied) {
-  // a chosen or tuned tile configuration means the separate kernels
-  if (p == D3S_BF16 || (d != 2 && d != 4) || c->tile_config >= 0 || c->autotune) return false;
+  // a chosen tile configuration means the separate kernels
+  if (p == D3S_BF16 || (d != 2 && d != 4) || c->tile_config >= 0) return false;
   const bool r2l = dir == D3S_R2L;
   FParams f{};
   f.na = r2l ? mr : ml;

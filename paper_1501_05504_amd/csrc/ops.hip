@@ -116,25 +116,29 @@ void heff_product(Ctx* c, d3s_prec p, int ml, int d, int mr, int wl, int wr, con
     *fused = 0;
   }
   if (ev) D3S_HIP(hipEventRecord(ev[0], c->stream));
-  if (front_wmap(c, p, D3S_L2R, ml, d, mr, wl, wr, L, W, psi, T2, (long)wr * mr, 1.0, true)) {
-    // GEMM-1 and the W-map in one launch: timed as GEMM-1
-    if (ev) {
-      *fused = 1;
-      D3S_HIP(hipEventRecord(ev[1], c->stream));
-    }
-  } else {
-    // GEMM-1's B operand psi[x][(t,y)] runs along N; a copy psi^T[(t,y)][x]
-    // runs along K, which keeps the LDS staging of B in 16-byte vector stores
-    // (the transposing stores cost most in BF16).  Counted in GEMM-1's time.
-    const size_t esz = (p == D3S_F64) ? 8 : (p == D3S_F32 ? 4 : 2);
-    transpose_any(c, (int)esz, psi, ml, (long)d * mr, psiT);
-    GemmArgs g1{ml * wl, d * mr, ml, L, ml, true, 0, psiT, ml, true, 0, T1, (long)d * mr, 0, 1.0, 0.0, 1};
-    g1.part = part;
-    g1.part_cap = part_cap;
-    if (plain) gemm(c, p, g1);
-    else tuned_gemm(c, p, g1);
+  // GEMM-1's B operand psi[x][(t,y)] runs along N; a copy psi^T[(t,y)][x]
+  // runs along K, which keeps the LDS staging of B in 16-byte vector stores
+  // (the transposing stores cost most in BF16).  Counted in GEMM-1's time.
+  GemmArgs g1{ml * wl, d * mr, ml, L, ml, true, 0, psiT, ml, true, 0, T1, (long)d * mr, 0, 1.0, 0.0, 1};
+  g1.part = part;
+  g1.part_cap = part_cap;
+  auto front = [&] { return front_wmap(c, p, D3S_L2R, ml, d, mr, wl, wr, L, W, psi, T2, (long)wr * mr, 1.0, true); };
+  auto separate = [&](auto&& gemm1) {
+    transpose_any(c, (p == D3S_F64) ? 8 : (p == D3S_F32 ? 4 : 2), psi, ml, (long)d * mr, psiT);
+    gemm1();
     if (ev) D3S_HIP(hipEventRecord(ev[1], c->stream));
     wmap_l2r(c, p, T1, W, T2, (long)wr * mr, ml, d, mr, wl, wr, 1.0);
+  };
+  bool one;                              // in one launch: timed as GEMM-1
+  if (!plain && c->autotune && c->tile_config < 0) {
+    one = tuned_first(c, p, g1, d, front, separate);
+  } else {
+    one = front();
+    if (!one) separate([&] { gemm(c, p, g1); });
+  }
+  if (ev && one) {
+    *fused = 1;
+    D3S_HIP(hipEventRecord(ev[1], c->stream));
   }
   if (ev) D3S_HIP(hipEventRecord(ev[2], c->stream));
   GemmArgs g2{ml * d, mr, wr * mr, T2, (long)wr * mr, true, 0, R, (long)wr * mr, true, 0, out, mr, 0,
