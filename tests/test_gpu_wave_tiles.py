@@ -340,3 +340,30 @@ def test_map_rule_edges(ctx, ml, mr, w):
             assert float(err.max() / ref(lambda v: v).abs().max()) < 3e-5
         else:
             assert bool((err <= 2.0 ** -8 * ref(torch.abs)).all())
+
+
+@pytest.mark.parametrize("dt, mlp, mr, wr", [(torch.float64, 33, 1040, 8), (torch.float64, 70, 1030, 8), (torch.float32, 30, 2060, 8),
+                                             (torch.float64, 1000, 1939, 6), (torch.float64, 2960, 1480, 5),
+                                             (torch.float32, 2960, 1480, 5)])
+def test_split_sums_equal_unsplit(ctx, dt, mlp, mr, wr):
+    """Sums that the rules split over the grid (few wave tiles of a very long sum;
+    workgroup tiles of a large product) against the same product unsplit: that
+    the split ran shows in the rounding, its result agrees with the unsplit one
+    and with the contraction in FP64, and a second run is bitwise the same."""
+    gen = torch.Generator(device=DEV).manual_seed(mlp)
+    Lt, R, Cm = [torch.randn(s, generator=gen, device=DEV, dtype=dt) for s in [(mlp, wr, mlp), (mr, wr, mr), (mlp, mr)]]
+    outs = []
+    try:
+        for on in (True, False, True):
+            ctx.set_splitk(on)
+            out = torch.full((mlp, mr), float("nan"), dtype=dt, device=DEV)
+            ctx.apply_cwf(Lt, R, Cm, out)
+            outs.append(out)
+    finally:
+        ctx.set_splitk(True)
+    T = torch.matmul(Lt.double().reshape(mlp * wr, mlp), Cm.double()).reshape(mlp, wr * mr)
+    ref = torch.matmul(T, R.double().reshape(mr, wr * mr).t().contiguous())
+    scale = float(ref.abs().max())
+    tol = 1e-12 if dt == torch.float64 else 3e-5
+    assert all(float((o.double() - ref).abs().max()) < tol * scale for o in outs)
+    assert torch.equal(outs[0], outs[2]) and not torch.equal(outs[0], outs[1])
