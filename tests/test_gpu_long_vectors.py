@@ -71,12 +71,11 @@ def test_lanczos_of_long_vectors(ctx, ml, d, mr, steps):
 
 def test_long_vectors_in_the_captured_step(ctx):
     """The step of the block sweeps that reads its index on the device (captured
-    once, replayed): a Heisenberg chain of 18 sites with one trivial sector has
-    vectors of up to 2 x 512 x 512 elements.  Its bonds hold every state, so the
-    energy is the ground state's: not above that of Sz sectors with 96 states
-    (vectors below 65536) but for the solver's tolerance, and not below it by
-    more than that truncation, some 1e-8, can cost."""
-    l = 18
+    once, replayed): a Heisenberg chain of 20 sites with one trivial sector has
+    vectors of up to 512 x 2 x 600 elements.  Its energy is not above that of Sz
+    sectors with 96 states (vectors below 65536) but for the solver's tolerance,
+    and not below it by more than their truncation, some 1e-8, can cost."""
+    l = 20
     mpo = abi.heisenberg_mpo(l)
     none = np.zeros_like(np.array(abi.SPIN_HALF_CHARGES))
 
@@ -90,5 +89,5 @@ def test_long_vectors_in_the_captured_step(ctx):
         return stats.energy
     chan = abi.mpo_spin_charges(1)
     ref = run(np.array(abi.SPIN_HALF_CHARGES), chan, 96, 8)
-    e = run(none, np.zeros_like(chan), 512, 4)
+    e = run(none, np.zeros_like(chan), 600, 4)
     assert ref - 1e-6 < e < ref + 1e-10
