@@ -8,10 +8,11 @@
 // autotuning is switched on).  Where the rule would run GEMM-1 and the W-map of
 // H_eff in one launch, that is timed against the tuned GEMM-1 and the launches
 // around it (whole product in FP64, d = 4, w = 6, with the rule's choices among the
-// candidates and without: 37 x 29 11.3 / 27.0 us, 256 x 250 43.6 / 62.0).  Grouped block plans: all six tile configurations of the grouped launch are
-// timed on scratch buffers right after the plan is built.  Tuning is skipped
-// while a stream is being captured into a graph and for products that accumulate
-// into C (beta != 0).
+// candidates and without: 37 x 29 11.3 / 27.0 us, 256 x 250 43.6 / 62.0).
+// Grouped block plans: all six tile configurations of the grouped launch are
+// timed on scratch buffers right after the plan is built.
+// Tuning is skipped while a stream is being captured into a graph and for
+// products that accumulate into C (beta != 0).
 #include <fstream>
 #include <sstream>
 

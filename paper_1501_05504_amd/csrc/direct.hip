@@ -5,11 +5,12 @@
 // What bounds a short product is the latency of a load against the few K
 // steps of a tile, and the idle compute units of a launch of few large
 // workgroups.  An FP64 (FP32) MFMA of 16x16x4 keeps a SIMD busy for 64 (32)
-// cycles and needs only 16 (8) bytes per lane, so wave tiles of 32x32 to 64x32
-// are fed by L1 and L2 (16-32 bytes per cycle and compute unit); small tiles
-// give many waves, the K steps of a tile can be shared by the waves of a
-// workgroup (summed through LDS in a fixed order), and up to two K steps of
-// each wave are in flight in registers.
+// cycles and needs only 16 (8) bytes per lane, so wave tiles of 32x32, 64x32 and
+// 32x64 are fed by L1 and L2 (16-32 bytes per cycle and compute unit), and those of
+// 16x16, which read twice as much, serve where the chip would otherwise be idle;
+// small tiles give many waves, the K steps of a tile can be shared by the waves of
+// a workgroup (summed through LDS in a fixed order), and up to two K steps of each
+// wave are in flight in registers.
 //
 // Fragments: a K step covers 128 bytes of K (16 doubles, 32 floats).  Lane
 // group g = lane / 16 holds the two 16-byte pieces [16 g, 16 g + 16) and
@@ -597,16 +598,17 @@ bool direct_dispatch(Ctx* c, const GemmArgs& g) {
   //  - fewer 32x32 tiles than compute units: eight waves a tile while each
   //    gets two K steps or more, else four; very long sums are split over the
   //    grid too, which costs a summing launch (about 5 us);
-  //  - long sums: 64x32 tiles of four waves once there are two for each compute
-  //    unit (2048 x 512 x 3072: 106 us, 32x32 tiles of four waves 111 us), before
-  //    that 32x32 ones (1200 x 280 x 1680: 33 against 43 us, 1600 x 400 x 2400:
-  //    66 against 76 us; FP32 36 against 44 us);
+  //  - long sums: 64x32 tiles of four waves once there are nearly two for each
+  //    compute unit, 900 tiles of 32x32 (2048 x 512 x 3072, 1024 tiles: 106 us,
+  //    32x32 tiles of four waves 111 us), before that 32x32 ones (1200 x 280 x 1680,
+  //    342 tiles: 33 against 43 us, 1600 x 400 x 2400, 650: 66 against 76 us; FP32
+  //    36 against 44 us);
   //  - short sums: four waves a 32x32 tile while there are fewer tiles than
   //    SIMDs (768 x 512 x 128: 7.2 us, one wave 8.3 us), one wave then
   //    (1536 x 1000 x 256: 21.5 us, four waves 24.4 us), and 32x64 tiles once
   //    these give every SIMD two (2400 x 3102 x 517: 150 us, 32x32 173 us).
   int splits = 1;
-  if (t32 <= 320 && g.batch == 1 && steps >= 512 && t32 <= 128 && !c->splitk_off) {
+  if (t32 <= 128 && g.batch == 1 && steps >= 512 && !c->splitk_off) {
     splits = (int)std::min<long>(512 / t32, steps / 64);
     if (g.part) splits = (int)std::min<size_t>((size_t)splits, g.part_cap / (sizeof(AT) * (size_t)g.M * g.N));
   }
@@ -701,8 +703,10 @@ bool front_dispatch(Ctx* c, bool r2l, bool copied, FParams p) {
     }
   }
   auto go = [&](auto m, auto n) {
-    if (r2l) front_launch<S, decltype(m)::value, decltype(n)::value, true>(c, p, sh);
-    else front_launch<S, decltype(m)::value, decltype(n)::value, false>(c, p, sh);
+    if constexpr (f64) {                 // right to left: expansion and environments, in FP64 only
+      if (r2l) return front_launch<S, decltype(m)::value, decltype(n)::value, true>(c, p, sh);
+    }
+    front_launch<S, decltype(m)::value, decltype(n)::value, false>(c, p, sh);
   };
   using I1 = std::integral_constant<int, 1>;
   using I2 = std::integral_constant<int, 2>;
@@ -754,6 +758,7 @@ bool front_wmap(Ctx* c, d3s_prec p, d3s_dir dir, int ml, int d, int mr, int wl, 
   // a chosen tile configuration means the separate kernels
   if (p == D3S_BF16 || (d != 2 && d != 4) || c->tile_config >= 0) return false;
   const bool r2l = dir == D3S_R2L;
+  if (r2l && p != D3S_F64) return false;
   FParams f{};
   f.na = r2l ? mr : ml;
   f.wx = r2l ? wr : wl;

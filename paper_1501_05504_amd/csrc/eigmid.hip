@@ -29,7 +29,6 @@ namespace {
 constexpr int kTail = 96;        // columns left to the tail
 constexpr int kLeafMax = 64;
 constexpr int kWg = 256;
-constexpr int kVecs = 1;         // eigenvectors per wave of the back-transformation
 
 struct Head {
   unsigned long long top;        // bits of the largest absolute entry
@@ -425,24 +424,18 @@ __global__ __launch_bounds__(kWg)
 void back_kernel(const double* __restrict__ Z, const double* __restrict__ V, const double* __restrict__ tauv,
                  const double* __restrict__ ev, int n, double* __restrict__ out, double* __restrict__ evals,
                  const Head* __restrict__ head, int* __restrict__ info) {
-  const int lane = threadIdx.x & 63, j0 = (blockIdx.x * (kWg / 64) + (threadIdx.x >> 6)) * kVecs;
-  if (j0 >= n) return;
-  double z[kVecs][NE], val[kVecs];
-  int rank[kVecs];
+  const int lane = threadIdx.x & 63, j = blockIdx.x * (kWg / 64) + (threadIdx.x >> 6);
+  if (j >= n) return;
+  double z[NE], cnt = 0.0;
+  const double val = ev[j];
 #pragma unroll
-  for (int q = 0; q < kVecs; ++q) {
-    const int j = min(j0 + q, n - 1);
-    val[q] = ev[j];
-    double cnt = 0.0;
-#pragma unroll
-    for (int i = 0; i < NE; ++i) {
-      const int c = lane + 64 * i;
-      z[q][i] = c < n ? Z[(long)j * n + c] : 0.0;
-      const double x = c < n ? ev[c] : INFINITY;
-      cnt += (x < val[q] || (x == val[q] && c < j)) ? 1.0 : 0.0;
-    }
-    rank[q] = (int)sum64(cnt);
+  for (int i = 0; i < NE; ++i) {
+    const int c = lane + 64 * i;
+    z[i] = c < n ? Z[(long)j * n + c] : 0.0;
+    const double x = c < n ? ev[c] : INFINITY;
+    cnt += (x < val || (x == val && c < j)) ? 1.0 : 0.0;
   }
+  const int rank = (int)sum64(cnt);
   // groups of G reflections, the next group's on their way meanwhile
   constexpr int G = NE <= 8 ? 4 : 2;
   double va[G][NE], vb[G][NE], ta[G], tb[G];
@@ -457,16 +450,14 @@ void back_kernel(const double* __restrict__ Z, const double* __restrict__ V, con
   };
   auto apply = [&](const double (&x)[G][NE], const double (&t)[G]) {
 #pragma unroll
-    for (int g = 0; g < G; ++g)
+    for (int g = 0; g < G; ++g) {
+      double y = 0.0;
 #pragma unroll
-      for (int q = 0; q < kVecs; ++q) {
-        double y = 0.0;
+      for (int i = 0; i < NE; ++i) y = fma(z[i], x[g][i], y);
+      y = t[g] * sum64(y);
 #pragma unroll
-        for (int i = 0; i < NE; ++i) y = fma(z[q][i], x[g][i], y);
-        y = t[g] * sum64(y);
-#pragma unroll
-        for (int i = 0; i < NE; ++i) z[q][i] = fma(-y, x[g][i], z[q][i]);
-      }
+      for (int i = 0; i < NE; ++i) z[i] = fma(-y, x[g][i], z[i]);
+    }
   };
   load(va, ta, n - 3);
   for (int k = n - 3; k >= 0; k -= 2 * G) {
@@ -475,18 +466,13 @@ void back_kernel(const double* __restrict__ Z, const double* __restrict__ V, con
     load(va, ta, k - 2 * G);
     apply(vb, tb);
   }
-  const int scale = scale_of(head);
 #pragma unroll
-  for (int q = 0; q < kVecs; ++q)
-    if (j0 + q < n) {
-#pragma unroll
-      for (int i = 0; i < NE; ++i) {
-        const int c = lane + 64 * i;
-        if (c < n) out[(long)rank[q] * n + c] = z[q][i];
-      }
-      if (lane == 0) evals[rank[q]] = ldexp(val[q], scale);
-    }
-  if (j0 == 0 && lane == 0) *info = head->info;
+  for (int i = 0; i < NE; ++i) {
+    const int c = lane + 64 * i;
+    if (c < n) out[(long)rank * n + c] = z[i];
+  }
+  if (lane == 0) evals[rank] = ldexp(val, scale_of(head));
+  if (j == 0 && lane == 0) *info = head->info;
 }
 
 template <int NE>
@@ -554,7 +540,7 @@ bool solve(Ctx* c, int n, double* A, double* evals, int* info) {
     }
     std::swap(Z, Z2);
   }
-  const int pv = kVecs * (kWg / 64);
+  const int pv = kWg / 64;                 // a wave per vector
   hipLaunchKernelGGL(back_kernel<NE>, dim3((n + pv - 1) / pv), dim3(kWg), 0, st, Z, V, tau, ev, n, A, evals, head, info);
   D3S_HIP(hipGetLastError());
   return true;
