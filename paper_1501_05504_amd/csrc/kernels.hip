@@ -81,8 +81,9 @@ void wmap_l2r_kernel(const Tin* __restrict__ T1, const Tc* __restrict__ Wg, Tout
 // runs over k in the order of wmap_l2r_kernel, so a product does not depend on
 // which of the two ran.  With one point a thread every broadcast read of four W
 // entries (8 cycles of the LDS that four SIMDs share) serves four multiply-adds
-// of one wave; here 16.  T1 FP32 to T2 BF16 at m = 2048, d =
-// 4, w = 6: 113 us (160 us), 604 MB at 5.3 TB/s, the rate of a copy.
+// of one wave; here 16.  T1 FP32 to T2 BF16, d = 4, w = 6, behind the GEMM that
+// writes T1: m = 1920 111 us (152 us), 2048 143 to 160 us (159 to 164 us), 2500 185
+// us (236 us), 4.2 to 4.8 TB/s, the rate of a copy.
 template <typename T> struct alignas(4 * sizeof(T)) Vec4 { T v[4]; };
 
 template <typename Tin, typename Tout, typename Tc, int MAXK>
@@ -235,10 +236,13 @@ void wmap_l2r_t(Ctx* c, const void* T1, const void* W, void* out, long ld_out, i
     // 640 0.95 and 700 x 700 0.86 of the time; d = 2, w = 5, 384 x 384 1.09 and 512 x
     // 512 0.99).  Nor may a row's second workgroup be nearly empty (FP32, w = 6,
     // 1200 x 1200 1.15 of the time, 1400 1.00, 1600 0.99, 1800 0.88; BF16, w = 8,
-    // 1200 1.19, 1536 0.95).
+    // 1200 1.19, 1536 0.95).  FP32 rows that large tensors stream from memory gain
+    // nothing with many inputs a point (w = 6, 2048 159 against 149 us, 2500 234
+    // against 230; d = 2, w = 8, 2500 145 against 152).
     const long rw = (mr + 255) / 256, waves = (long)ml * mr / 256 * mr / (256 * rw);
-    const int two = K < 16 ? 0 : sizeof(Tout) == 4 ? (K <= 24 ? 1550 : 1700) : K <= 16 ? 0 : K <= 24 ? 1100 : 1500;
-    if (fits && K <= 32 && waves >= (K <= 16 ? 780 : 1030) && mr >= 192 && (mr <= 1024 || mr >= two) &&
+    const int two = K < 16 ? 0 : sizeof(Tout) == 4 ? (K <= 24 ? 1550 : 1700) : K <= 16 ? 0 : K <= 24 ? 1250 : 1500;
+    const int last = sizeof(Tout) == 4 && K > 16 ? 2000 : 1 << 30;
+    if (fits && K <= 32 && waves >= (K <= 16 ? 780 : 1030) && mr >= 192 && (mr <= 1024 || (mr >= two && mr < last)) &&
         mr % 4 == 0 && ld_out % 4 == 0 &&
         reinterpret_cast<uintptr_t>(T1) % (4 * sizeof(Tin)) == 0 &&
         reinterpret_cast<uintptr_t>(out) % (4 * sizeof(Tout)) == 0) {

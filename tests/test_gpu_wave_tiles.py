@@ -312,8 +312,8 @@ def test_small_map_of_whole_vectors(ctx, m, w):
     assert best(m) <= 1.25 * ragged
 
 
-@pytest.mark.parametrize("ml, mr", [(1876, 192), (1876, 188), (580, 600), (510, 600), (330, 1096), (330, 1100), (240, 1548),
-                                    (240, 1552), (340, 1496), (401, 1500), (200, 1696), (200, 1700)])
+@pytest.mark.parametrize("ml, mr", [(1876, 192), (1876, 188), (580, 600), (510, 600), (280, 1248), (280, 1252), (240, 1548),
+                                    (240, 1552), (340, 1496), (401, 1500), (200, 1696), (200, 1700), (180, 1996), (180, 2000)])
 @pytest.mark.parametrize("w", [6, 8])
 def test_map_rule_edges(ctx, ml, mr, w):
     """FP32 and BF16 products on both sides of the sizes at which the W-map
