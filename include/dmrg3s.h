@@ -148,7 +148,8 @@ d3s_status d3s_set_refinement(d3s_ctx ctx, double eta, int inner_max, double low
  * is the one chosen by d3s_set_eigensolver.  Each matrix is divided by its
  * largest diagonal entry before the solve and its eigenvalues scaled back
  * (rocSOLVER's divide and conquer loses accuracy in proportion to a small
- * matrix norm).  Synchronises; D3S_EDEVICE if an eigensolve did not converge. */
+ * matrix norm).  Synchronises; D3S_EDEVICE if an eigensolve did not converge,
+ * D3S_ENUMERIC for an infinite or NaN entry. */
 d3s_status d3s_eig_batched(d3s_ctx ctx, int n, int batch, double* A, double* W);
 /* Split-K of GEMMs whose tiles cannot fill the device (default on; the
  * partial products are summed in a fixed order, so results stay
