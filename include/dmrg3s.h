@@ -44,7 +44,7 @@ typedef enum {
   D3S_EINVAL = -1,   /* bad argument (shape, null pointer, enum) -- nothing was launched */
   D3S_ENOMEM = -2,   /* workspace allocation failed */
   D3S_EDEVICE = -3,  /* HIP or rocSOLVER error */
-  D3S_ENUMERIC = -4  /* non-finite energy or norm */
+  D3S_ENUMERIC = -4  /* non-finite energy, norm or matrix entry */
 } d3s_status;
 
 /* Arithmetic of the contractions.  Element types of the tensor pointers:

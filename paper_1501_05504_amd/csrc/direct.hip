@@ -20,7 +20,9 @@
 // All loads go through a buffer resource based at the tile's first element;
 // rows past the operand's edge get an offset outside the resource and read
 // as zeros without touching memory.  16-byte buffer loads need 4-byte
-// alignment only, so no size or leading dimension is slower than another.
+// alignment only, so no size or leading dimension takes other instructions; rows
+// that start off a 128-byte line cost long sums of large products L2 traffic (see
+// gemm_auto's rule).
 // The last K step, when it is not whole, is loaded element by element
 // (predicated), first of all, so that its latency overlaps the pipeline's
 // fill.
@@ -675,11 +677,10 @@ bool front_dispatch(Ctx* c, bool r2l, bool copied, FParams p) {
   // launches and their gaps 20 us.  Expansion and environments have no copy of
   // psi, a GEMM on its own layout and a W-map into other rows: 7 % more for the
   // GEMM, 3.3 TB/s, 10 us (m = 1024 right to left 801 / 831 us, 1200 left to
-  // right 1423 / 1483, 1800 4825 / 4625).  H_eff, d = 4,
-  // w = 6, this kernel against the launches, FP64: m = 300 51 / 68 us, 512
-  // 125 / 141, 800 433 / 444, 900 646 / 642, 1024 835 / 795, 1200 1452 / 1403, 1400
-  // 2466 / 2113, 1600 3211 / 3040; FP32: 300 35 / 49, 600 122 / 142, 800 236 /
-  // 230, 1024 458 / 427, 1400 1235 / 1117.
+  // right 1423 / 1483, 1800 4825 / 4625).  H_eff, d = 4, w = 6, this kernel against
+  // the launches, FP64: m = 300 51 / 68 us, 512 125 / 141, 800 433 / 444, 900 646 /
+  // 642, 1024 835 / 795, 1200 1452 / 1403, 1400 2466 / 2113, 1600 3211 / 3040; FP32:
+  // 300 35 / 49, 600 122 / 142, 800 236 / 230, 1024 458 / 427, 1400 1235 / 1117.
   const double t_front = 2.0 * tiles2 * kFrontRows * 128.0 * p.K / (f64 ? 60e12 : 102e12);
   const double rows = (double)p.na * p.wx, cols = (double)p.nq * d;
   const double t_gemm = gemm_estimate(f64 ? D3S_F64 : D3S_F32, (int)rows, (int)cols, p.K).seconds;
